@@ -113,6 +113,18 @@ __device__ inline void quantise_group32(const typename E::T* rowp, const int* ch
   codes_out = make_uint4(w[0], w[1], w[2], w[3]);
 }
 
+// fresh ? a : b, as two selects on finished addresses (the address that is
+// not taken is computed but never read).  Written as a branch, the compiler
+// shared the row arithmetic and kept the base pointer in one register that
+// the join of `r < tok_end` overwrote for every lane with r >= tok_begin:
+// rows past the range were then read relative to the prefill output.
+__device__ inline const uint8_t* select_row(bool fresh, const uint8_t* a, const uint8_t* b) {
+  uint64_t pa = reinterpret_cast<uint64_t>(a), pb = reinterpret_cast<uint64_t>(b);
+  asm("" : "+v"(pa), "+v"(pb));  // opaque: neither address is folded into a branch
+  typedef const __attribute__((address_space(1))) uint8_t* global_ptr;
+  return (const uint8_t*)reinterpret_cast<global_ptr>(fresh ? pa : pb);
+}
+
 // Copies rows [r_lo, r_hi) of one unit's V from the prefill output to the cache.
 __device__ inline void copy_v_rows(const IndexArgs& a, int s, int g, size_t unit, int r_lo, int r_hi, int es) {
   const int rbv = a.d_v * es;
@@ -225,8 +237,8 @@ __global__ __launch_bounds__(kIdxThreads) void index_rows_kernel(const IndexArgs
         if (idx < nch) {
           const int r = pr0 + idx / cpr, cc = idx % cpr;
           fresh[u] = a.k_src && r >= a.tok_begin && r < a.tok_end;
-          const uint8_t* src = fresh[u] ? a.k_src + ((size_t(s) * S + (r - a.tok_begin)) * a.H_kv + g) * rb
-                                        : a.k + (unit * a.T + r) * rb;
+          const uint8_t* src = select_row(fresh[u], a.k_src + ((size_t(s) * S + size_t(r - a.tok_begin)) * a.H_kv + g) * rb,
+                                          a.k + (unit * a.T + r) * rb);
           x[u] = ld16(src + cc * 16);
         }
       }

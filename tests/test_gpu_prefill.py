@@ -114,6 +114,47 @@ def test_prefill_writes_cache_and_indices(name, kind):
 
 
 @pytest.mark.parametrize("name", sorted(CASES))
+def test_prefill_of_a_range_with_later_rows_present(name):
+    """Rows [t0, t1) rewritten in a cache that already holds the rows before
+    and after them (ctx_len past t1, both edges inside blocks): the blocks of
+    the range are summarised over every valid row, those outside the range
+    read from the cache."""
+    c = get_case(name)
+    cfg = c.cfg
+    t0, t1 = 70, 170
+    K, V = c.k.clone(), None if cfg.mla else c.v.clone()
+    K[:, :, t0:t1] = SENTINEL
+    if V is not None:
+        V[:, :, t0:t1] = SENTINEL
+    kmax = torch.full((cfg.batch, cfg.h_kv, c.m_max, cfg.d_qk), SENTINEL, dtype=K.dtype, device="cuda")
+    kmin = torch.full_like(kmax, SENTINEL)
+    codes = torch.full((cfg.batch, cfg.h_kv, cfg.max_ctx, cfg.d_c // 2), 0xAA, dtype=torch.uint8, device="cuda")
+    qparams = torch.full((cfg.batch, cfg.h_kv, cfg.max_ctx, cfg.d_c // 32, 2), SENTINEL, dtype=torch.float32,
+                         device="cuda")
+    tls.tls_prefill_kv(c.layout, _src(c.k, t0, t1), None if cfg.mla else _src(c.v, t0, t1), c.ctx, c.ch, t0, t1, K, V,
+                       kmax, kmin, codes, qparams)
+    torch.cuda.synchronize()
+    b0, b1 = t0 // cfg.block, -(-t1 // cfg.block)
+    for s in range(cfg.batch):
+        n = int(c.ctx_host[s])
+        assert n > b1 * cfg.block, "the last block of the range is full"
+        for g in range(cfg.h_kv):
+            what = f"{name} unit {(s, g)}"
+            assert torch.equal(_bits(K[s, g, :n]), _bits(c.k[s, g, :n])), what + " K rows"
+            if V is not None:
+                assert torch.equal(_bits(V[s, g, :n]), _bits(c.v[s, g, :n])), what + " V rows"
+            Ku, _ = c.unit_kv_f64(s, g)
+            mx, mn = O.block_summaries(Ku, n, cfg.block)
+            np.testing.assert_array_equal(synth.torch_to_f64(kmax[s, g, b0:b1]), mx[b0:b1], err_msg=what + " kmax")
+            np.testing.assert_array_equal(synth.torch_to_f64(kmin[s, g, b0:b1]), mn[b0:b1], err_msg=what + " kmin")
+            assert bool((kmax[s, g, b1:] == SENTINEL).all()) and bool((kmax[s, g, :b0] == SENTINEL).all()), what
+            cod, qp = O.token_index(Ku, n, c.ch_host[g])
+            assert np.array_equal(codes[s, g, t0:t1].cpu().numpy(), cod[t0:t1]), what + " codes"
+            np.testing.assert_array_equal(qparams[s, g, t0:t1].cpu().numpy(), qp[t0:t1], err_msg=what + " qparams")
+            assert bool((codes[s, g, t1:] == 0xAA).all()) and bool((codes[s, g, :t0] == 0xAA).all()), what
+
+
+@pytest.mark.parametrize("name", sorted(CASES))
 def test_prefill_equals_separate_builders(name):
     """The fused call and the two standalone builders over the written cache
     give the same bytes."""
