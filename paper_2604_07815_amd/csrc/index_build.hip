@@ -366,6 +366,255 @@ __global__ __launch_bounds__(kIdxThreads) void index_rows_kernel(const IndexArgs
   }
 }
 
+// ---------------------------------------------------------------------------
+// The same work for the row widths in use (CPR 16-byte pieces per K row: 8,
+// 16, 32, or 72 for the 576-dim MLA row), one work-group of NT = RG * CPR
+// threads per block.  HBM-bound, so the block's whole K (and V) is requested
+// before anything waits: thread (row group rg, piece cc) holds rows rg, rg +
+// RG, ... of one column in registers, 2 to 8 loads in flight for K and as
+// many for V, stores them to the cache from there, folds its column's
+// maximum and minimum without touching LDS, and stages the rows once for the
+// quantiser, which takes four lanes per (token, 32-channel group), eight
+// channels each in registers.  The general kernel above waits four times
+// (V, then K, four loads at a time), folds the summary row by row through LDS
+// and quantises with one lane per group, i.e. with one wave of four where
+// d_c = 32.
+// ---------------------------------------------------------------------------
+template <class E>
+__device__ inline void fold_max_min(const uint4& v, float (&mx)[E::kVec], float (&mn)[E::kVec]) {
+  float f[E::kVec];
+  unpack16<E>(v, f);
+#pragma unroll
+  for (int e = 0; e < E::kVec; ++e) {
+    mx[e] = fmaxf(mx[e], f[e]);
+    mn[e] = fminf(mn[e], f[e]);
+  }
+}
+
+// Summary values (exact copies of inputs; + 0.0f turns -0.0 into +0.0) as one
+// 16-byte piece.
+template <class E>
+__device__ inline uint4 pack_summary(const float (&f)[E::kVec]) {
+  uint32_t w[4];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    if constexpr (E::kIsBf16)
+      w[k] = uint32_t(f32_to_bf16(f[2 * k] + 0.0f)) | (uint32_t(f32_to_bf16(f[2 * k + 1] + 0.0f)) << 16);
+    else
+      w[k] = __float_as_uint(f[k] + 0.0f);
+  }
+  return make_uint4(w[0], w[1], w[2], w[3]);
+}
+
+__device__ inline float quad_min(float v) {
+  v = fminf(v, __int_as_float(dpp_perm<0xB1>(__float_as_int(v))));
+  return fminf(v, __int_as_float(dpp_perm<0x4E>(__float_as_int(v))));
+}
+__device__ inline float quad_max(float v) {
+  v = fmaxf(v, __int_as_float(dpp_perm<0xB1>(__float_as_int(v))));
+  return fmaxf(v, __int_as_float(dpp_perm<0x4E>(__float_as_int(v))));
+}
+
+constexpr int kIdxBlockRows = 64;  // B of the fast kernel
+
+template <class E, int CPR, int NT, bool VROWS>
+__global__ __launch_bounds__(NT) void index_block_kernel(const IndexArgs a) {
+#pragma clang fp contract(off)
+  using S = typename E::T;
+  constexpr int es = int(sizeof(S)), V = E::kVec;
+  constexpr int RG = NT / CPR, LPT = kIdxBlockRows / RG;  // row groups, rows per thread
+  constexpr int RB = CPR * 16;                            // bytes per K row
+  constexpr int TSW = RB / 4 + 4;                         // words per staged row (one 16-byte piece of padding)
+  static_assert(RG * CPR == NT && LPT * RG == kIdxBlockRows && NT >= 2 * CPR, "row geometry");
+  extern __shared__ uint4 smem4[];
+  uint32_t* t32 = reinterpret_cast<uint32_t*>(smem4);
+  int* s_ch = reinterpret_cast<int*>(t32 + kIdxBlockRows * TSW);
+  const int s = blockIdx.z, g = blockIdx.x, tid = threadIdx.x;
+  int n = a.ctx_lens[s];
+  if (n < 0 || n > a.T) {
+    if (tid == 0 && blockIdx.y == 0 && g == 0) set_error(a.err, 1u);
+    n = n < 0 ? 0 : a.T;
+  }
+  const int hi = min(a.tok_end, n);
+  const int i = a.tok_begin / kIdxBlockRows + int(blockIdx.y);
+  const int r0 = i * kIdxBlockRows;
+  if (r0 >= hi) return;  // block past the valid end of the range
+  const int r1 = min(r0 + kIdxBlockRows, n);
+  const size_t unit = size_t(s) * a.H_kv + g;
+  const size_t srows = size_t(a.tok_end - a.tok_begin);
+  const int rg = tid / CPR, cc = tid % CPR;
+
+  // every row of the block, clamped to its last valid one (a repeated row
+  // changes no maximum): from the prefill output inside the range, else from
+  // the cache
+  uint8_t* krow = a.k + (unit * a.T + r0) * RB + cc * 16;
+  uint4 x[LPT], y[VROWS ? LPT : 1];
+  uint32_t fresh = 0;  // bit u: row rg + u * RG is new (and valid: the range ends at hi)
+  const uint8_t* ksrc = nullptr;
+  const uint8_t* vsrc = nullptr;
+  size_t sstride = 0;  // bytes between consecutive rows of a head in the prefill output
+  if (a.k_src) {
+    const size_t first = (size_t(s) * srows + size_t(r0 - a.tok_begin)) * a.H_kv + g;  // (wraps below the range; unread)
+    sstride = size_t(a.H_kv) * RB;
+    ksrc = a.k_src + first * RB + cc * 16;
+    if constexpr (VROWS) vsrc = a.v_src + first * RB + cc * 16;
+  }
+  if (a.k_src && r0 >= a.tok_begin && r0 + kIdxBlockRows <= hi) {  // uniform: the whole block is new
+    fresh = (1u << LPT) - 1u;
+#pragma unroll
+    for (int u = 0; u < LPT; ++u) x[u] = ld16_stream(ksrc + size_t(rg + u * RG) * sstride);
+    if constexpr (VROWS) {
+#pragma unroll
+      for (int u = 0; u < LPT; ++u) y[u] = ld16_stream(vsrc + size_t(rg + u * RG) * sstride);
+    }
+  } else {
+#pragma unroll
+    for (int u = 0; u < LPT; ++u) {
+      const int r = r0 + rg + u * RG, rc = min(r, r1 - 1);
+      const bool in = a.k_src && rc >= a.tok_begin && rc < hi;
+      fresh |= in && r == rc ? 1u << u : 0u;
+      x[u] = ld16(select_row(in, ksrc + size_t(rc - r0) * sstride, krow + size_t(rc - r0) * RB));
+    }
+    if constexpr (VROWS) {
+#pragma unroll
+      for (int u = 0; u < LPT; ++u)
+        if ((fresh >> u) & 1u) y[u] = ld16(vsrc + size_t(rg + u * RG) * sstride);
+    }
+  }
+  // the group's channel ids, requested behind the rows
+  const bool do_block = a.flags & kIdxBlock, do_token = a.flags & kIdxToken;
+  if (do_token) {
+    for (int c = tid; c < a.d_c; c += NT) {
+      int ch = a.channels[g * a.d_c + c];
+      if (ch < 0 || ch >= a.d) {  // caller-supplied channel id out of range: read channel 0
+        set_error(a.err, 32u);
+        ch = 0;
+      }
+      s_ch[c] = ch;
+    }
+  }
+  float mx[V], mn[V];
+#pragma unroll
+  for (int e = 0; e < V; ++e) {
+    mx[e] = -__builtin_inff();
+    mn[e] = __builtin_inff();
+  }
+#pragma unroll
+  for (int u = 0; u < LPT; ++u) {
+    const int rr = rg + u * RG;
+    if (do_token) *reinterpret_cast<uint4*>(t32 + rr * TSW + cc * 4) = x[u];
+    if ((fresh >> u) & 1u) *reinterpret_cast<uint4*>(krow + size_t(rr) * RB) = x[u];
+    if (do_block) fold_max_min<E>(x[u], mx, mn);
+  }
+  if constexpr (VROWS) {
+    uint8_t* vrow = a.v + (unit * a.T + r0) * RB + cc * 16;
+#pragma unroll
+    for (int u = 0; u < LPT; ++u)
+      if ((fresh >> u) & 1u) *reinterpret_cast<uint4*>(vrow + size_t(rg + u * RG) * RB) = y[u];
+  }
+
+  // ---- token index of the rows inside [tok_begin, hi) ----
+  if (do_token) {
+    __syncthreads();
+    const int lo = max(r0, a.tok_begin) - r0, up = min(r0 + kIdxBlockRows, hi) - r0;
+    const int ngroups = a.d_c / 32;
+    // item: lane quarter of eight channels, row, group (uniform over a wave)
+    for (int k = tid; k < 4 * kIdxBlockRows * ngroups; k += NT) {
+      const int sub = k & 3, rr = (k >> 2) & (kIdxBlockRows - 1), grp = k / (4 * kIdxBlockRows);
+      if (rr < lo || rr >= up) continue;  // uniform over a quad of lanes
+      const S* rowp = reinterpret_cast<const S*>(t32 + rr * TSW);
+      const int4 c0 = *reinterpret_cast<const int4*>(s_ch + grp * 32 + sub * 8);
+      const int4 c1 = *reinterpret_cast<const int4*>(s_ch + grp * 32 + sub * 8 + 4);
+      const int ch[8] = {c0.x, c0.y, c0.z, c0.w, c1.x, c1.y, c1.z, c1.w};
+      float f[8];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) f[j] = E::to_f(rowp[ch[j]]);
+      float lo_v = __builtin_inff(), hi_v = -__builtin_inff();
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        lo_v = fminf(lo_v, f[j]);
+        hi_v = fmaxf(hi_v, f[j]);
+      }
+      lo_v = quad_min(lo_v);
+      hi_v = quad_max(hi_v);
+      const float scale = (hi_v - lo_v) / 15.0f;  // IEEE float32 subtract and divide
+      uint32_t word = 0u;
+      if (scale != 0.0f) {  // codes as in quantise_group32
+        const float rcp = __builtin_amdgcn_rcpf(scale);
+        uint32_t near = 0;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+          const float q = (f[j] - lo_v) * rcp;
+          near |= uint32_t(!(fabsf(__builtin_amdgcn_fractf(q) - 0.5f) > kNearHalf && q < 16.0f)) << j;
+          word |= uint32_t(fminf(fmaxf(__builtin_rintf(q), 0.0f), 15.0f)) << (4 * j);
+        }
+        for (; near != 0; near &= near - 1) {  // rare: the IEEE quotient
+          const int j = __builtin_ctz(near);
+          const float q = fminf(fmaxf(__builtin_rintf((E::to_f(rowp[s_ch[grp * 32 + sub * 8 + j]]) - lo_v) / scale), 0.0f), 15.0f);
+          word = (word & ~(0xFu << (4 * j))) | (uint32_t(q) << (4 * j));
+        }
+      }
+      const size_t trow = unit * size_t(a.T) + (r0 + rr);
+      *reinterpret_cast<uint32_t*>(a.codes + trow * (a.d_c / 2) + grp * 16 + sub * 4) = word;
+      if (sub == 0) *reinterpret_cast<float2*>(a.qparams + (trow * ngroups + grp) * 2) = make_float2(scale, lo_v + 0.0f);
+    }
+  }
+
+  // ---- block summary: combine the row groups and store ----
+  if (do_block) {
+    // partials in the staged rows' place, exact in the input type: [RG][CPR] maxima, then minima
+    uint4* part = smem4;
+    static_assert(2 * NT * 16 <= kIdxBlockRows * TSW * 4, "partials fit in the staged rows");
+    if (do_token) __syncthreads();  // the quantiser is done with the rows
+    part[rg * CPR + cc] = pack_summary<E>(mx);
+    part[NT + rg * CPR + cc] = pack_summary<E>(mn);
+    __syncthreads();
+    if (tid < 2 * CPR) {
+      const bool low = tid >= CPR;
+      const int c = low ? tid - CPR : tid;
+      float fx[V], fn[V];
+#pragma unroll
+      for (int e = 0; e < V; ++e) {
+        fx[e] = -__builtin_inff();
+        fn[e] = __builtin_inff();
+      }
+#pragma unroll 8
+      for (int p = 0; p < RG; ++p) fold_max_min<E>(part[(low ? NT : 0) + p * CPR + c], fx, fn);
+      uint8_t* dst = (low ? a.kmin : a.kmax) + (unit * a.m_max + i) * RB + c * 16;
+      const uint4 wx = pack_summary<E>(fx), wn = pack_summary<E>(fn);
+      *reinterpret_cast<uint4*>(dst) = make_uint4(low ? wn.x : wx.x, low ? wn.y : wx.y, low ? wn.z : wx.z, low ? wn.w : wx.w);
+    }
+  }
+}
+
+template <class E, int CPR, int NT>
+static void launch_index_block(const IndexArgs& a, int nblk, int batch, hipStream_t st) {
+  const size_t lds = size_t(kIdxBlockRows) * (CPR * 16 + 16) + size_t(a.d_c) * sizeof(int);
+  // heads fastest: the heads' rows of one token are adjacent in the prefill output
+  const dim3 grid(unsigned(a.H_kv), unsigned(nblk), unsigned(batch));
+  if (a.v_src) index_block_kernel<E, CPR, NT, true><<<grid, NT, lds, st>>>(a);
+  else index_block_kernel<E, CPR, NT, false><<<grid, NT, lds, st>>>(a);
+}
+
+// The fast kernel's shapes: blocks of 64 rows, K rows of 8, 16, 32 or 72
+// 16-byte pieces, and V rows (if written) as wide as the K rows.
+static bool launch_index_block_for(const Problem& P, const IndexArgs& a, int rb, int nblk, hipStream_t st) {
+  if (P.B != kIdxBlockRows || (a.v_src && P.d_v != P.d_qk) || nblk > 65535) return false;
+  if (P.dtype == 1) {
+    switch (rb / 16) {
+      case 8: launch_index_block<BF16, 8, 256>(a, nblk, P.b, st); return true;
+      case 16: launch_index_block<BF16, 16, 256>(a, nblk, P.b, st); return true;
+      case 72: launch_index_block<BF16, 72, 576>(a, nblk, P.b, st); return true;
+      default: return false;
+    }
+  }
+  switch (rb / 16) {
+    case 16: launch_index_block<F32, 16, 256>(a, nblk, P.b, st); return true;
+    case 32: launch_index_block<F32, 32, 256>(a, nblk, P.b, st); return true;
+    default: return false;
+  }
+}
+
 size_t index_rows_lds_bytes(int rb, int rows_per_pass, int d_c, int es) {
   const int wpr = rb / 4;
   const int nph = wpr <= kIdxThreads / 2 ? kIdxThreads / wpr : 1;
@@ -403,6 +652,7 @@ static hipError_t launch_index_rows(const Problem& P, const void* k_src, const v
   a.flags = flags;
   a.err = err;
   const int nblk = (tok_end + P.B - 1) / P.B - tok_begin / P.B;  // blocks overlapping the range
+  if (launch_index_block_for(P, a, rb, nblk, st)) return hipGetLastError();
   dim3 grid(unsigned(nblk), unsigned(P.H_kv), unsigned(P.b));
   const size_t lds = index_rows_lds_bytes(rb, a.rows_per_pass, (flags & kIdxToken) ? P.d_c : 0, es);
   if (P.dtype == 1) index_rows_kernel<BF16><<<grid, kIdxThreads, lds, st>>>(a);
