@@ -75,6 +75,12 @@ __device__ inline uint4 ld16_stream(const void* p) {
   return r;
 }
 
+// Non-temporal 16-byte store for data not read back soon.
+__device__ inline void st16_stream(void* p, const uint4& v) {
+  typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+  __builtin_nontemporal_store(u32x4{v.x, v.y, v.z, v.w}, reinterpret_cast<u32x4*>(p));
+}
+
 // ---------------------------------------------------------------------------
 // Wave reductions (xor butterflies over `width` lanes, width a power of two)
 // ---------------------------------------------------------------------------
