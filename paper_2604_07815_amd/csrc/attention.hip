@@ -292,6 +292,13 @@ int attn_tokens_per_split(const Problem& P) {
   return gqa_tokens_per_split(P);
 }
 
+// (MLA shapes other than 32 heads x 576 / 512: the vector kernel's capacity,
+// also where a matrix-core kernel would take more)
+long attn_max_tokens(const Problem& P) {
+  const bool wide = !P.mla || (mla_mfma_ok(P) && P.G == 32);
+  return long(kMaxSplits) * (wide ? attn_tokens_per_split(P) : kMlaCt);
+}
+
 int attn_splits_for(const Problem& P, int K_t, int requested) {
   const int cap = attn_tokens_per_split(P);
   const int need = (K_t + cap - 1) / cap;  // fewest splits the work-group capacity allows

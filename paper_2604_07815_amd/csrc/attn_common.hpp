@@ -39,6 +39,70 @@ __device__ inline int list_token(const TokenList& L, size_t unit, int p, int n, 
   return p < n ? p : -1;
 }
 
+// s_waitcnt immediates (gfx9 encoding): vmcnt in [3:0] and [15:14],
+// expcnt in [6:4], lgkmcnt in [11:8].
+__host__ __device__ constexpr int waitcnt_vm(int n) { return (n & 15) | ((n >> 4) << 14) | (7 << 4) | (15 << 8); }
+constexpr int kWaitLgkm0 = 0xC07F;
+
+// Work-group barrier for LDS traffic only: completes this wave's LDS
+// accesses, then synchronises, leaving global loads (including the
+// asynchronous LDS gathers of the next chunk) in flight.  The
+// wavefront-scope fences keep the compiler from moving memory accesses
+// across it.
+__device__ inline void lds_barrier() {
+  __builtin_amdgcn_s_waitcnt(kWaitLgkm0);
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+typedef __attribute__((address_space(3))) void lds_void;
+
+// Asynchronous 16-byte-per-lane gather into LDS: lane i reads 16 bytes at
+// `src` and the wave writes them to lds + 16*i.  Issued through inline asm so
+// that the compiler does not order later LDS accesses behind it; completion
+// is tracked explicitly with s_waitcnt vmcnt and a work-group barrier before
+// the data is read, and the target buffer is not read or rewritten while a
+// gather into it is in flight.  The s_nop is the wait state that gfx9 requires
+// between a scalar write of M0 and an LDS-DMA load that reads it (the compiler
+// inserts none inside an asm block).
+__device__ inline void gather16_to_lds(const void* src, const void* lds) {
+  // the LDS destination is wave-uniform; readfirstlane puts it in an SGPR
+  const uint32_t off = uint32_t(__builtin_amdgcn_readfirstlane(int(reinterpret_cast<uintptr_t>((lds_void*)lds))));
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off nt" : : "s"(off), "v"(src) : "m0");
+}
+
+typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8_t;
+typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4_t;
+
+// Compiler-level ordering point for LDS accesses around the inline-asm
+// gathers (emits no instruction at wavefront scope).
+__device__ inline void wave_fence() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
+
+// Max / sum over the lanes i, i^16, i^32, i^48 (one per DPP row) through the
+// gfx950 row-swap permutes; every lane gets the same bits.
+__device__ inline float xrows_max(float v) {
+  const auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+  const auto b = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
+}
+__device__ inline float xrows_sum(float v) {
+  const auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = __uint_as_float(a[0]) + __uint_as_float(a[1]);
+  const auto b = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return __uint_as_float(b[0]) + __uint_as_float(b[1]);
+}
+
+typedef short i16x4_t __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) i16x4_t lds_i16x4;
+
+__device__ inline short bf16_bits_rne(float f) {
+  uint32_t u = __float_as_uint(f);  // finite, non-negative here
+  u += 0x7fffu + ((u >> 16) & 1u);
+  return short(u >> 16);
+}
+
 __device__ inline float exp_or_zero(float x) { return x == -INFINITY ? 0.f : expf(x); }
 
 // Transposing butterfly all-reduce over the MASK*2 lanes of a lane group:

@@ -120,6 +120,7 @@ struct TokenList {
   int B;
 };
 int attn_tokens_per_split(const Problem& P);  // token capacity of one attention work-group
+long attn_max_tokens(const Problem& P);       // longest work list the library accepts
 int attn_splits_for(const Problem& P, int K_t, int requested);
 // Whole-unit attention (one work-group per unit writes the output directly;
 // no partials, no merge).  Valid when gqa_whole_ok().

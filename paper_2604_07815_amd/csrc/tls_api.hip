@@ -99,7 +99,7 @@ tls_status check_attention(const Problem& P, int K_t) {
     if (P.d_qk != P.d_v || (P.d_qk != 128 && P.d_qk != 64)) return TLS_ERR_UNSUPPORTED;
     if (P.G != 1 && P.G != 2 && P.G != 4 && P.G != 8) return TLS_ERR_UNSUPPORTED;
   }
-  if (long(K_t) > long(tls::kMaxSplits) * tls::attn_tokens_per_split(P)) return TLS_ERR_UNSUPPORTED;
+  if (long(K_t) > tls::attn_max_tokens(P)) return TLS_ERR_UNSUPPORTED;
   return TLS_OK;
 }
 

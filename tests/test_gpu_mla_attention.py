@@ -1,0 +1,85 @@
+"""The absorbed-MLA attention on given token ids, at the edges of its chunks
+(32 or 64 tokens), splits and work-groups: list lengths around one and two
+chunks, empty entries (single ones, a whole chunk, the whole list), more
+work-groups than compute units, both head counts, and logits that grow along
+the list, so that the running maximum has to be raised after the first chunk.
+
+Bound: bf16 has eight significant bits, so rounding to nearest is off by up to
+2^-8 of a value.  The probabilities are rounded before the second product (the
+normaliser is not) and the output once more, so an element may be off by
+2^-8 (sum_j w_j |v_j| + |o|); 1e-4 sum_j w_j |v_j| covers the fp32
+logits (576 products of magnitude ~1/576 each) and exponentials."""
+import math
+
+import pytest
+import torch
+
+import paper_2604_07815_amd as tls
+
+pytestmark = pytest.mark.gpu
+
+T = 1600
+
+
+def _inputs(heads, batch, seed, growing):
+    g = torch.Generator().manual_seed(seed)
+    q = (torch.randn((batch, heads, 576), generator=g) / 24).to(torch.bfloat16)
+    K = torch.randn((batch, 1, T, 576), generator=g)
+    if growing:  # base-2 logits rising by about 12 per 64 tokens along the first head's query
+        d = q[:, :1].float() / q[:, :1].float().norm(dim=-1, keepdim=True) ** 2
+        K = 0.1 * K + d.reshape(batch, 1, 1, 576) * (torch.arange(T) * (12 / 64 * math.log(2) * 24)).reshape(1, 1, T, 1)
+    assert K.shape == (batch, 1, T, 576)
+    return q, K.to(torch.bfloat16)
+
+
+def _check(q, K, ids, out, lse):
+    b, H, _ = q.shape
+    for s in range(b):
+        sel = ids[s, 0][ids[s, 0] >= 0].long()
+        if len(sel) == 0:
+            assert bool((out[s] == 0).all()) and bool((lse[s] == -math.inf).all())
+            continue
+        k = K[s, 0][sel].double()
+        v = k[:, :512]
+        z = (q[s].double() @ k.T) / 24.0
+        w = torch.softmax(z, -1)
+        o, mag = w @ v, w @ v.abs()
+        tol = 2.0 ** -8 * (mag + o.abs()) + 1e-4 * mag
+        err = (out[s].double() - o).abs()
+        assert bool((err <= tol).all()), (s, float((err / tol).max()))
+        assert torch.allclose(lse[s].double(), torch.logsumexp(z, -1), rtol=1e-5, atol=1e-4)
+
+
+def _decode(q, K, ids, splits):
+    b, H, _ = q.shape
+    layout = tls.make_layout(b, H, 1, 576, 512, T, index_channels=64, dtype=torch.bfloat16, mla_shared_kv=True)
+    k_t = ids.shape[-1]
+    ws = tls.alloc_workspace(layout, 1, k_t)
+    out = torch.empty((b, H, 512), dtype=torch.bfloat16, device="cuda")
+    lse = torch.empty((b, H), dtype=torch.float32, device="cuda")
+    n = torch.full((b,), T, dtype=torch.int32, device="cuda")
+    tls.tls_sparse_decode(layout, q.cuda(), tls.KV(K.cuda(), None), n, None, None, None, None, None, 1, k_t, None,
+                          ids.cuda(), out, lse, None, None, ws, attn_splits=splits)
+    assert tls.tls_check_device_error(ws) == 0
+    return out.cpu(), lse.cpu()
+
+
+@pytest.mark.parametrize("heads", [16, 32])
+@pytest.mark.parametrize("k_t,splits", [(1, 0), (31, 1), (33, 1), (64, 0), (65, 1), (129, 2), (500, 0), (1025, 0),
+                                        (1500, 128)])
+def test_list_lengths_and_splits(heads, k_t, splits):
+    q, K = _inputs(heads, 3, 100 + k_t, False)
+    g = torch.Generator().manual_seed(k_t)
+    ids = torch.stack([torch.randperm(T, generator=g)[:k_t].sort().values for _ in range(3)]).reshape(3, 1, k_t).int()
+    ids[1, 0, torch.rand(k_t, generator=g) < 0.3] = -1  # single empty entries
+    ids[2, 0, :64] = -1                                  # whole empty chunks
+    _check(q, K, ids, *_decode(q, K, ids, splits))
+
+
+@pytest.mark.parametrize("heads", [16, 32])
+@pytest.mark.parametrize("splits", [1, 2, 128])
+def test_rising_logits_raise_the_maximum(heads, splits):
+    q, K = _inputs(heads, 2, 7, True)
+    ids = torch.arange(1024).reshape(1, 1, -1).repeat(2, 1, 1).int()
+    ids[1] = ids[1].flip(-1)
+    _check(q, K, ids, *_decode(q, K, ids, splits))
