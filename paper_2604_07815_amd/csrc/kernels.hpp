@@ -27,7 +27,7 @@ constexpr int kTokenSlotsPerWG = 256;
 
 // Workspace carving (byte offsets from the workspace base, 256-aligned).
 struct Workspace {
-  size_t err, xfer, qpn, bscores, bids, logits, stats, keys, kinfo, tids, po, plse, dkeys, dstats, total;
+  size_t err, xfer, qpn, bscores, bids, logits, stats, keys, kinfo, tids, po, plse, dkeys, dstats, dhist, total;
   int n_tchunks;  // token-score work-groups per unit
 };
 // Regions of the workspace, as a mask: a route of a call names the regions
@@ -40,7 +40,8 @@ enum : unsigned {
   kWsTids = 16u,      // token ids when the caller takes none
   kWsSplit = 32u,     // split-attention partials and their lse
   kWsDense = 64u,     // keys and statistics of the token-level operator
-  kWsAll = 127u,
+  kWsDenseHist = 128u,  // its key-bucket counts (optional: without them the keys are streamed once per radix pass)
+  kWsAll = 255u,
 };
 Workspace plan_workspace(const Problem& P, int K_b, int K_t, unsigned regions = kWsAll, int nsplit = kMaxSplits);
 
@@ -90,12 +91,15 @@ hipError_t launch_token_select_fused(const Problem& P, const void* q, const uint
                                      hipStream_t st);
 
 // Token-level selection over every valid token of each unit (the token-only
-// operator): alpha keys [units][T] and per-chunk statistics in the workspace.
+// operator): alpha keys [units][T], per-chunk statistics and (nullable) key
+// bucket counts in the workspace.
 bool ds_supported(const Problem& P);
 size_t ds_stats_floats(const Problem& P);
+size_t ds_hist_words(const Problem& P);
 hipError_t launch_token_select_dense(const Problem& P, const void* q, const uint8_t* codes, const float* qparams,
                                      const int32_t* channels, const int32_t* ctx_lens, int K_t, float* stats,
-                                     uint32_t* keys, int32_t* token_ids, uint32_t* err, hipStream_t st);
+                                     uint32_t* keys, uint32_t* hist, int32_t* token_ids, uint32_t* err,
+                                     hipStream_t st);
 
 struct KvView {
   const void* k;

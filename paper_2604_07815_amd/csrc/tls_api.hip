@@ -158,6 +158,7 @@ Workspace plan_workspace(const Problem& P, int K_b, int K_t, unsigned regions, i
   take(&w.plse, kWsSplit, U * ns * P.G * sizeof(float));
   take(&w.dkeys, kWsDense, U * size_t(P.T) * sizeof(uint32_t));  // token-only operator
   take(&w.dstats, kWsDense, ds_stats_floats(P) * sizeof(float));
+  take(&w.dhist, kWsDenseHist, ds_hist_words(P) * sizeof(uint32_t));
   w.total = off;
   return w;
 }
@@ -470,7 +471,13 @@ tls_status token_level_decode(const Problem& P, const void* q, const tls_kv_view
   tls::Workspace W;
   void* ws = nullptr;
   uint32_t* err = nullptr;
-  st = tgt.bind(P, K_b > 0 ? K_b : 1, K_t, regions, nsplit, &W, &ws, &err);
+  // with the bucket counts where they fit the library's scratch too
+  bool counts = true;
+  st = tgt.bind(P, K_b > 0 ? K_b : 1, K_t, regions | tls::kWsDenseHist, nsplit, &W, &ws, &err);
+  if (st == TLS_ERR_WORKSPACE_TOO_SMALL && tgt.compact) {
+    counts = false;
+    st = tgt.bind(P, K_b > 0 ? K_b : 1, K_t, regions, nsplit, &W, &ws, &err);
+  }
   if (st != TLS_OK) return st;
   auto mark = [&](int i) {
     if (ev) (void)hipEventRecord(ev[i], stream);
@@ -480,8 +487,8 @@ tls_status token_level_decode(const Problem& P, const void* q, const tls_kv_view
   mark(2);
   int32_t* to = token_ids_out ? token_ids_out : at<int32_t>(ws, W.tids);
   const hipError_t e = tls::launch_token_select_dense(P, q, codes, qparams, channels, ctx_lens, K_t,
-                                                      at<float>(ws, W.dstats), at<uint32_t>(ws, W.dkeys), to, err,
-                                                      stream);
+                                                      at<float>(ws, W.dstats), at<uint32_t>(ws, W.dkeys),
+                                                      counts ? at<uint32_t>(ws, W.dhist) : nullptr, to, err, stream);
   mark(3);
   mark(4);
   mark(5);

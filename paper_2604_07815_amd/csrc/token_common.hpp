@@ -15,6 +15,10 @@ __device__ inline void unpack_nibbles8(uint32_t w, float* f) {
   f[6] = float(lo >> 24);           f[7] = float(hi >> 24);
 }
 
+// The alpha key of a candidate: alpha >= +0 has the key bits | 2^31 (as
+// float_key); a NaN alpha (NaN inputs only) ranks as 0.
+__device__ inline uint32_t alpha_key(float a) { return __float_as_uint(fmaxf(a, 0.f)) | 0x80000000u; }
+
 // Candidate slot -> token position.  slot = i*B + o addresses offset o of the
 // i-th entry of the unit's block list; valid when that entry is a block id
 // >= 0 and the token lies below ctx_len.  Ids past the last block set

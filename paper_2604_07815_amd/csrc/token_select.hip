@@ -365,10 +365,6 @@ __device__ inline void write_unit_info(const int32_t* bl, int b_first, int K_b, 
   }
 }
 
-// The alpha key of a candidate: alpha >= +0 has the key bits | 2^31 (as
-// float_key); a NaN alpha (NaN inputs only) ranks as 0.
-__device__ inline uint32_t alpha_key(float a) { return __float_as_uint(fmaxf(a, 0.f)) | 0x80000000u; }
-
 __global__ __launch_bounds__(256) void token_alpha_kernel(
     const float* __restrict__ logits, const float* __restrict__ stats, int n_tchunks,
     const int32_t* __restrict__ block_ids, int K_b, const int32_t* __restrict__ ctx_lens, int H_kv, int G,

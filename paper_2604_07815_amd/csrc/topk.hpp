@@ -382,6 +382,62 @@ __device__ void wg_topk_regs(const uint32_t (&kr)[EPT], int k, int32_t* out, int
   }
 }
 
+// wg_topk_regs where a first pass has already found the bucket of the k-th
+// largest key: the keys in the registers (no fewer than k) are those at or
+// above `lowest`, the bucket's lower end, `cnt` of them in the bucket [lowest,
+// lowest + 2^kTopkSpreadShift), of which the largest `remaining` are taken.
+// The caller has run topk_prepare before a work-group barrier.
+struct TopkStart {
+  uint32_t lowest;
+  int remaining, cnt;
+};
+
+template <int NT, int EPT, class Map>
+__device__ void wg_topk_resume(const uint32_t (&kr)[EPT], int k, int32_t* out, int out_cap, Map map,
+                               uint32_t* scratch, const TopkStart& start) {
+  const int lane = threadIdx.x & 63;
+  uint32_t* cg = scratch + align4w_c(kTopkPasses * kTopkHistWords) + 64;
+  uint32_t* ce = cg + kTopkMaxEPT * kTopkMaxNW;
+  uint32_t prefix = start.lowest, pmask = ~((1u << kTopkSpreadShift) - 1u);
+  int remaining = start.remaining, bits_left = kTopkSpreadShift;
+  uint32_t cnt_T = uint32_t(start.cnt);
+  if (cnt_T == uint32_t(remaining)) {  // the bucket is taken whole (lowest >= 1)
+    prefix -= 1u;
+    remaining = 0;
+    bits_left = 0;
+  }
+  for (int pass = 0; bits_left > 0; ++pass) {
+    const int nb = bits_left < 8 ? bits_left : 8, shift = bits_left - nb;
+    uint32_t* h = scratch + kTopkHistWords * pass;
+    uint32_t* hc = h + (lane % kTopkHistCopies) * kTopkHistStride;
+#pragma unroll
+    for (int j = 0; j < EPT; ++j) {
+      const uint32_t key = kr[j];
+      if (key != kInvalidKey && (key & pmask) == prefix) atomicAdd(&hc[__builtin_amdgcn_ubfe(key, uint32_t(shift), 8u)], 1u);
+    }
+    __syncthreads();
+    const TopkDigit dg = topk_scan_wave(h, remaining);
+    prefix |= dg.digit << shift;
+    remaining -= int(dg.above);
+    pmask |= ((1u << nb) - 1u) << shift;
+    bits_left -= nb;
+    cnt_T = dg.cnt;
+    if (dg.cnt == uint32_t(remaining) && bits_left > 0) {
+      prefix -= 1u;
+      remaining = 0;
+      bits_left = 0;
+    }
+  }
+  uint32_t T = prefix;
+  int r = remaining;
+  if (r > 0 && uint32_t(r) == cnt_T) {
+    T -= 1u;
+    r = 0;
+  }
+  topk_compact_tile<NT, EPT>(kr, T, r, 0, 0, out, nullptr, map, cg, ce);
+  for (int i = k + int(threadIdx.x); i < out_cap; i += NT) out[i] = -1;
+}
+
 // The same selection over keys[0, n) in global memory, for more keys than
 // the registers hold (token-level selection over a whole context): every
 // pass streams the keys in tiles of NT*16; after the first pass the keys

@@ -1,0 +1,99 @@
+"""Token-level selection over a whole context (MODE_TOKEN_SPARSE) on each of
+its kernels: the matrix-core kernels for bf16 with 1 to 8 heads (one or more
+32-channel groups) and with 16 or 32 heads, the vector kernel for fp32 and the
+other index widths; lengths around the kernels' chunks (1024, 4096 tokens) and
+the selection's tiles (16384), budgets from one token to more than the context,
+all scores equal (ties to the lowest positions), with more equal keys than the
+candidate list holds.
+
+The reference is alpha in float64 from the index rows.  An fp32 alpha is off
+by under 2e-6 of its value here (logits below 32 in base 2, each rounded at
+2^-24 of that), so the selected set has to hold every token whose alpha is
+above the K_t-th by more than 1e-5 of it, and none below it by more."""
+import math
+
+import pytest
+import torch
+
+import paper_2604_07815_amd as tls
+
+pytestmark = pytest.mark.gpu
+
+CASES = [
+    # (G, d_qk, d_c, dtype, mla)
+    (1, 64, 32, torch.bfloat16, False), (2, 128, 64, torch.bfloat16, False), (4, 128, 32, torch.bfloat16, False),
+    (8, 128, 32, torch.bfloat16, False), (8, 128, 96, torch.bfloat16, False), (4, 128, 32, torch.float32, False),
+    (16, 576, 64, torch.bfloat16, True), (32, 576, 128, torch.bfloat16, True), (32, 576, 64, torch.bfloat16, True),
+    (16, 576, 128, torch.bfloat16, True), (32, 576, 32, torch.bfloat16, True),
+]
+
+
+def _setup(G, d, d_c, dtype, mla, lens, seed, zero_q=False):
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    b, hkv, T = len(lens), 1 if mla else 2, max(lens)
+    dv = 512 if mla else d
+    q = torch.randn((b, G * hkv, d), generator=g, device="cuda") / (24.0 if mla else 1.0)
+    q = (q * 0 if zero_q else q).to(dtype)
+    K = torch.randn((b, hkv, T, d), generator=g, device="cuda").to(dtype)
+    V = None if mla else torch.randn((b, hkv, T, dv), generator=g, device="cuda").to(dtype)
+    n = torch.tensor(lens, dtype=torch.int32, device="cuda")
+    gc = torch.Generator().manual_seed(seed)
+    ch = torch.stack([torch.randperm(d, generator=gc)[:d_c].sort().values for _ in range(hkv)]).int().cuda()
+    layout = tls.make_layout(b, G * hkv, hkv, d, dv, T, index_channels=d_c, dtype=dtype, mla_shared_kv=mla)
+    codes = torch.zeros((b, hkv, T, d_c // 2), dtype=torch.uint8, device="cuda")
+    qp = torch.zeros((b, hkv, T, d_c // 32, 2), dtype=torch.float32, device="cuda")
+    tls.tls_build_token_index(layout, K, n, ch, 0, T, codes, qp)
+    return layout, q, K, V, n, ch, codes, qp
+
+
+def _alpha(q, codes, qp, ch, n, s, g, G):
+    c = codes[s, g, :n].long()
+    x = torch.stack([c & 15, c >> 4], -1).reshape(n, -1, 32).double()
+    x = (x * qp[s, g, :n, :, :1].double() + qp[s, g, :n, :, 1:].double()).reshape(n, -1)
+    qq = q[s, g * G:(g + 1) * G].double()[:, ch[g].long()]
+    return torch.softmax(qq @ x.T / math.sqrt(q.shape[-1]), -1).mean(0)
+
+
+def _select(layout, q, K, V, n, ch, codes, qp, k_t, noalloc=False):
+    b, hkv = K.shape[:2]
+    out = torch.empty((b, q.shape[1], 512 if V is None else V.shape[-1]), dtype=q.dtype, device="cuda")
+    tids = torch.full((b, hkv, k_t), -7, dtype=torch.int32, device="cuda")
+    args = (layout, q, tls.KV(K, V), n, None, None, codes, qp, ch, 1, k_t, None, None, out, None, None, tids)
+    if noalloc:
+        tls.tls_sparse_decode_noalloc(*args, None, mode=tls.MODE_TOKEN_SPARSE)
+    else:
+        ws = tls.alloc_workspace(layout, 1, k_t)
+        tls.tls_sparse_decode(*args, ws, mode=tls.MODE_TOKEN_SPARSE)
+        assert tls.tls_check_device_error(ws) == 0
+    torch.cuda.synchronize()
+    return tids
+
+
+@pytest.mark.parametrize("lens,k_t", [((1, 63, 1025), 1), ((4095, 4097, 300), 500), ((16383, 16385, 9000), 2048)])
+@pytest.mark.parametrize("G,d,d_c,dtype,mla", CASES)
+def test_selected_tokens(G, d, d_c, dtype, mla, lens, k_t):
+    a = _setup(G, d, d_c, dtype, mla, lens, 11 * G + d_c)
+    layout, q, K, V, n, ch, codes, qp = a
+    tids = _select(*a, k_t).cpu()
+    for s, ln in enumerate(lens):
+        for g in range(K.shape[1]):
+            ids = tids[s, g]
+            kk = min(k_t, ln)
+            assert bool((ids[kk:] == -1).all())
+            ids = ids[:kk].long()
+            assert bool((ids[1:] > ids[:-1]).all()) and int(ids[0]) >= 0 and int(ids[-1]) < ln
+            alpha = _alpha(q, codes, qp, ch, ln, s, g, G).cpu()
+            kth = alpha.sort(descending=True).values[kk - 1]
+            chosen = torch.zeros(ln, dtype=torch.bool)
+            chosen[ids] = True
+            assert bool(chosen[alpha > kth * (1 + 1e-5)].all()), (s, g)
+            assert not bool(chosen[alpha < kth * (1 - 1e-5)].any()), (s, g)
+
+
+@pytest.mark.parametrize("noalloc", [False, True])
+@pytest.mark.parametrize("G,d,d_c,dtype,mla", [CASES[2], CASES[5], CASES[7]])
+def test_equal_scores_take_the_lowest_positions(G, d, d_c, dtype, mla, noalloc):
+    lens = (20000, 700, 5000)  # 20000 equal keys: more than the candidate list holds
+    a = _setup(G, d, d_c, dtype, mla, lens, 5, zero_q=True)
+    tids = _select(*a, 600, noalloc=noalloc).cpu()
+    assert bool((tids == torch.arange(600, dtype=torch.int32)).all())
