@@ -21,11 +21,12 @@ constexpr int kAttnCT = 64;      // tokens per chunk
 constexpr int kAttnMaxTPW = 512;  // tokens per work-group (fp32 kernel)
 constexpr int kAttnMaxTPWBf16 = 1024;  // tokens per work-group (bf16 matrix-core kernel)
 
-template <class E, int D, int G>
-__global__ __launch_bounds__(256) void attn_gqa_kernel(
+// The body, for work-groups of at most NCH chunks.
+template <class E, int D, int G, int NCH>
+__device__ __forceinline__ void attn_gqa_body(
     const typename E::T* __restrict__ q, const typename E::T* __restrict__ Kp,
     const typename E::T* __restrict__ Vp, const int32_t* __restrict__ slot_map, int64_t n_slots,
-    const TokenList tl, const int32_t* __restrict__ ctx_lens, int H_q, int H_kv, int T,
+    const TokenList& tl, const int32_t* __restrict__ ctx_lens, int H_q, int H_kv, int T,
     int B, int m_max, int K_t, int tpw, float sigma, float* __restrict__ po, float* __restrict__ plse,
     uint32_t* err) {
   using S = typename E::T;
@@ -42,8 +43,9 @@ __global__ __launch_bounds__(256) void attn_gqa_kernel(
   static_assert(LPR * 16 == ROWB && RPI * LPR == 64 && NI * RPI == RPW, "row geometry");
   __shared__ __attribute__((aligned(16))) uint8_t sK0[CT * ROWB];
   __shared__ __attribute__((aligned(16))) uint8_t sV0[CT * ROWB];
-  __shared__ __attribute__((aligned(16))) uint8_t sK1[CT * ROWB];
-  __shared__ __attribute__((aligned(16))) uint8_t sV1[CT * ROWB];
+  constexpr int CT1 = NCH > 1 ? CT : 1;  // one chunk needs no second buffer
+  __shared__ __attribute__((aligned(16))) uint8_t sK1[CT1 * ROWB];
+  __shared__ __attribute__((aligned(16))) uint8_t sV1[CT1 * ROWB];
   __shared__ float s_z[G][CT];
   __shared__ float s_m[G], s_l[G], s_sc[G];
 
@@ -59,7 +61,6 @@ __global__ __launch_bounds__(256) void attn_gqa_kernel(
 
   // this lane's gather rows for every chunk (row index within the unit's K/V
   // base, -1: skip); the lane's row group scores exactly these rows
-  constexpr int NCH = kAttnMaxTPW / CT;
   int rreg[NCH][NI];
 #pragma unroll
   for (int c = 0; c < NCH; ++c)
@@ -122,7 +123,7 @@ __global__ __launch_bounds__(256) void attn_gqa_kernel(
   // one chunk: wait for it, score, softmax update, P.V; prefetch the next
   auto step = [&](const int c, const int (&rows)[NI], const int (&next)[NI], const uint8_t* bk, const uint8_t* bv,
                   uint8_t* nk, uint8_t* nv) {
-    if (c + 1 < nch) {
+    if (NCH > 1 && c + 1 < nch) {
       issue(next, nk, nv);
       __builtin_amdgcn_s_waitcnt(waitcnt_vm(2 * NI));  // chunk c has landed
     } else {
@@ -226,6 +227,31 @@ __global__ __launch_bounds__(256) void attn_gqa_kernel(
     po[pbase * D + idx] = L > 0.f ? o / L : 0.f;
     if (idx % D == 0) plse[pbase + h] = L > 0.f ? s_m[h] + logf(L) : -INFINITY;
   }
+}
+
+template <class E, int D, int G>
+__global__ __launch_bounds__(256) void attn_gqa_kernel(
+    const typename E::T* __restrict__ q, const typename E::T* __restrict__ Kp,
+    const typename E::T* __restrict__ Vp, const int32_t* __restrict__ slot_map, int64_t n_slots,
+    const TokenList tl, const int32_t* __restrict__ ctx_lens, int H_q, int H_kv, int T,
+    int B, int m_max, int K_t, int tpw, float sigma, float* __restrict__ po, float* __restrict__ plse,
+    uint32_t* err) {
+  attn_gqa_body<E, D, G, kAttnMaxTPW / kAttnCT>(q, Kp, Vp, slot_map, n_slots, tl, ctx_lens, H_q, H_kv, T, B, m_max, K_t,
+                                                tpw, sigma, po, plse, err);
+}
+
+// Work-groups of one chunk (small budgets, or few units cut into many splits):
+// an eighth of the code, so that a launch does not spend its time fetching
+// instructions of chunks it does not have, no second buffer and no row table.
+template <class E, int D, int G>
+__global__ __launch_bounds__(256) void attn_gqa_chunk_kernel(
+    const typename E::T* __restrict__ q, const typename E::T* __restrict__ Kp,
+    const typename E::T* __restrict__ Vp, const int32_t* __restrict__ slot_map, int64_t n_slots,
+    const TokenList tl, const int32_t* __restrict__ ctx_lens, int H_q, int H_kv, int T,
+    int B, int m_max, int K_t, int tpw, float sigma, float* __restrict__ po, float* __restrict__ plse,
+    uint32_t* err) {
+  attn_gqa_body<E, D, G, 1>(q, Kp, Vp, slot_map, n_slots, tl, ctx_lens, H_q, H_kv, T, B, m_max, K_t, tpw, sigma, po,
+                            plse, err);
 }
 
 template <int D, int G, int NW, int TPWV, bool WHOLE>
@@ -343,9 +369,12 @@ static void launch_t(const Problem& P, const void* q, const KvView& kv, const To
         ctx_lens, P.H_q, P.H_kv, P.T, P.B, P.m_max, K_t, tpw, P.sigma, po, plse, nullptr, nullptr, err);
   } else {
     tpw = (tpw + kAttnCT - 1) / kAttnCT * kAttnCT;
-    attn_gqa_kernel<E, D, G><<<grid, 256, 0, st>>>((const S*)q, (const S*)kv.k, (const S*)kv.v, kv.slot_map,
-                                                   kv.n_slots, tl, ctx_lens, P.H_q, P.H_kv, P.T, P.B,
-                                                   P.m_max, K_t, tpw, P.sigma, po, plse, err);
+    auto go = [&](auto kern) {
+      kern<<<grid, 256, 0, st>>>((const S*)q, (const S*)kv.k, (const S*)kv.v, kv.slot_map, kv.n_slots, tl, ctx_lens,
+                                 P.H_q, P.H_kv, P.T, P.B, P.m_max, K_t, tpw, P.sigma, po, plse, err);
+    };
+    if (tpw == kAttnCT) go(attn_gqa_chunk_kernel<E, D, G>);
+    else go(attn_gqa_kernel<E, D, G>);
   }
 }
 

@@ -92,34 +92,9 @@ __device__ inline void ds_unit_norm(const float* st, int nc, float (*s_part)[G][
   }
 }
 
-// A packed dword of codes (channel 2i in the low nibble of byte i) as bf16
-// numbers 16 + c (bits 0x4180 | c << 3, exact), in the channel order 0, 2, 1,
-// 3, 4, 6, 5, 7 of a matrix operand.  Eight instructions; 16 is the smallest
-// offset for which one byte permute makes two codes, and 16 sum q~ comes off
-// the dot in fp32 before the row's scale multiplies it (dot16).
-__device__ inline uint4 codes_bf16(uint32_t w) {
-  constexpr uint32_t kHi = 0x41414141u;
-  uint32_t lo, hi;
-  asm("v_lshl_or_b32 %0, %1, 3, %2" : "=v"(lo) : "v"(w & 0x0f0f0f0fu), "s"(0x80808080u));
-  asm("v_and_or_b32 %0, %1, %2, %3" : "=v"(hi) : "v"(w >> 1), "v"(0x78787878u), "s"(0x80808080u));
-  return make_uint4(__builtin_amdgcn_perm(kHi, lo, 0x04010400u), __builtin_amdgcn_perm(kHi, hi, 0x04010400u),
-                    __builtin_amdgcn_perm(kHi, lo, 0x04030402u), __builtin_amdgcn_perm(kHi, hi, 0x04030402u));
-}
-// sum_c q~_c c_c from the product with 16 + c: the fma rounds once, at the
-// size of the result
-__device__ inline float dot16(float acc, float qsum) { return fmaf(-16.0f, qsum, acc); }
-// channel of position j (< 8) in that order
-__device__ inline int codes_chan(int j) { return (j & 4) | ((j & 1) << 1) | ((j >> 1) & 1); }
-
 // ---------------------------------------------------------------------------
-// bf16, G <= 8: a lane owns its tokens; 64 tokens of a wave are four tiles of
-// 16, and lane (lg, t16) owns token t16 of tile lg.  The code contraction runs
-// on v_mfma_f32_16x16x32_bf16: B = one tile's codes (the lanes' dwords
-// transposed over the lane groups with four swaps), A = four heads' q~ in the
-// rows 4 tl + r of tile tl and zeros elsewhere, so that the four tiles' dots
-// accumulate in one result whose lane (lg, t16) holds its own token's dots
-// with heads r: no rearranging.  The sums of q~ come from the same instructions
-// with B = 1.  Bound by HBM (24 bytes per token and pass at d_c = 32) and by
+// bf16, G <= 8: a lane owns its tokens, the code contraction runs on the matrix
+// cores (lane_dots).  Bound by HBM (24 bytes per token and pass at d_c = 32) and by
 // vector issue, 93 instructions per 64 tokens: 128 units of 73k tokens, 226
 // MB, take 45 us (pass 0) and 49 us (pass 1) against 78 us each on the vector
 // units, which spend some 200 instructions on extracting codes and
@@ -144,7 +119,6 @@ __global__ __launch_bounds__(kDsThreads, G <= 4 ? 4 : 2) void ds_score_mfma_kern
   __shared__ float s_red[kDsNW][G][2], s_mz[G][2];
   __shared__ uint32_t s_hist[KEYS ? kTopkHistWords : 1];
   const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
-  const int t16 = lane & 15, lg = lane >> 4;
   // pass 1 walks the chunks backwards: the rows that pass 0 read last may
   // still be in the Infinity Cache
   const int unit = KEYS ? int(gridDim.y - 1 - blockIdx.y) : int(blockIdx.y);
@@ -203,36 +177,7 @@ __global__ __launch_bounds__(kDsThreads, G <= 4 ? 4 : 2) void ds_score_mfma_kern
   const uint32_t bound = KEYS ? alpha_key(bsum * invG) : 0u;
   bf16x8_t qa[HS][4];  // A operand of each tile
   f32x4_t qsum[HS];    // the sums of q~ of the group
-  auto load_q = [&](int gr) {
-#pragma unroll
-    for (int hs = 0; hs < HS; ++hs) {
-      const uint4 row = *reinterpret_cast<const uint4*>(s_qt + ((gr * HS + hs) * 4 + (t16 & 3)) * 32 + lg * 8);
-      const uint4 one = make_uint4(0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u);
-      qsum[hs] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int tl = 0; tl < 4; ++tl) {
-        qa[hs][tl] = __builtin_bit_cast(bf16x8_t, t16 >> 2 == tl ? row : make_uint4(0, 0, 0, 0));
-        qsum[hs] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qa[hs][tl], __builtin_bit_cast(bf16x8_t, one), qsum[hs], 0, 0, 0);
-      }
-    }
-  };
-  // dots of one token with the heads' q~ on the group's channels
-  auto dots = [&](const uint4& c, f32x4_t (&acc)[HS]) {
-    // dword lg of tile tl's token t16
-    const auto a02 = __builtin_amdgcn_permlane32_swap(c.x, c.z, false, false);
-    const auto a13 = __builtin_amdgcn_permlane32_swap(c.y, c.w, false, false);
-    const auto b01 = __builtin_amdgcn_permlane16_swap(a02[0], a13[0], false, false);
-    const auto b23 = __builtin_amdgcn_permlane16_swap(a02[1], a13[1], false, false);
-    const uint32_t wd[4] = {b01[0], b01[1], b23[0], b23[1]};
-#pragma unroll
-    for (int hs = 0; hs < HS; ++hs) acc[hs] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int tl = 0; tl < 4; ++tl) {
-      const bf16x8_t b = __builtin_bit_cast(bf16x8_t, codes_bf16(wd[tl]));
-#pragma unroll
-      for (int hs = 0; hs < HS; ++hs) acc[hs] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qa[hs][tl], b, acc[hs], 0, 0, 0);
-    }
-  };
+  auto load_q = [&](int gr) { lane_operands<HS>(s_qt + gr * HS * 128, qa, qsum); };
   // a step's base-2 logits (pass 0), or those minus the maxima (pass 1), of the thread's tokens
   auto finish = [&](float (&l)[TPT][G], int st) {
     const int j = j0 + st * STEP + tid;
@@ -281,7 +226,7 @@ __global__ __launch_bounds__(kDsThreads, G <= 4 ? 4 : 2) void ds_score_mfma_kern
 #pragma unroll
       for (int t = 0; t < TPT; ++t) {
         f32x4_t acc[HS];
-        dots(cw[st & 1][t], acc);
+        lane_dots<HS>(cw[st & 1][t], qa, acc);
 #pragma unroll
         for (int h = 0; h < G; ++h) {
           const float qs = qsum[h / 4][h % 4];
@@ -313,7 +258,7 @@ __global__ __launch_bounds__(kDsThreads, G <= 4 ? 4 : 2) void ds_score_mfma_kern
 #pragma unroll
         for (int t = 0; t < TPT; ++t) {
           f32x4_t acc[HS];
-          dots(cw[1][t], acc);
+          lane_dots<HS>(cw[1][t], qa, acc);
 #pragma unroll
           for (int h = 0; h < G; ++h) {
             const float qs = qsum[h / 4][h % 4];

@@ -134,6 +134,201 @@ __global__ __launch_bounds__(256) void token_score_kernel(
   }
 }
 
+// One work-group's per-head maximum and sum of exponentials, from its waves'
+// (lane 0 of each has written s_red[wave][head] = {max, sum}).
+template <int NH>
+__device__ inline void write_chunk_stats(const float (*s_red)[NH][2], int G, float* st) {
+  __syncthreads();
+  if (int(threadIdx.x) < G) {
+    const int h = threadIdx.x;
+    float M = -INFINITY, Z = 0.f;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) M = fmaxf(M, s_red[w][h][0]);
+#pragma unroll
+    for (int w = 0; w < 4; ++w)
+      if (s_red[w][h][0] != -INFINITY) Z += s_red[w][h][1] * __expf(s_red[w][h][0] - M);
+    st[2 * h] = M;
+    st[2 * h + 1] = Z;
+  }
+}
+
+// The same for fp32 queries (and index widths without a matrix-core kernel)
+// with G = 1, 2, 4 or 8: a latency chain at the sizes it runs at, so the
+// loads leave in two rounds (block-list entry, context length and channel ids;
+// then q~ and the slot's rows) with one barrier, a row is dequantised in
+// registers and meets the heads' q~ of a channel in one LDS read.  The sums of
+// min and scale parts are not kept apart: sum_c q~_c (min + scale code_c) with
+// each term centred rounds less.  8 heads x 4096 tokens, K_b = 8: 9.4 -> 4 us.
+template <class E, int G>
+__global__ __launch_bounds__(256) void token_score_row_kernel(
+    const typename E::T* __restrict__ q, const uint8_t* __restrict__ codes, const float* __restrict__ qparams,
+    const int32_t* __restrict__ channels, const int32_t* __restrict__ block_ids, int K_b,
+    const int32_t* __restrict__ ctx_lens, int H_q, int H_kv, int d, int d_c, int B, int T, float sigma,
+    float* __restrict__ logits, float* __restrict__ stats, uint32_t* err) {
+  __shared__ __attribute__((aligned(16))) float s_q[kMaxGroups * 32 * G];  // [channel][head]
+  __shared__ float s_red[4][G][2];
+  const int unit = blockIdx.y, chunk = blockIdx.x;
+  const int s = unit / H_kv, g = unit % H_kv;
+  const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+  const int S = K_b * B, ngr = d_c / 32;
+  const int slot = chunk * kTokenSlotsPerWG + tid;
+  int n = ctx_lens[s];
+  const int blk = block_ids[size_t(unit) * K_b + min(tok_block(min(slot, S - 1), B), K_b - 1)];
+  int ch = tid < d_c ? channels[g * d_c + tid] : 0;  // d_c <= 256
+  n = n < 0 ? 0 : (n > T ? T : n);
+  const int m = (n + B - 1) / B;
+  if (ch < 0 || ch >= d) {
+    set_error(err, 32u);
+    ch = 0;
+  }
+  if (slot < S && blk >= m) set_error(err, 2u);
+  const int tok = blk * B + tok_offset(slot, B);
+  const bool valid = slot < S && blk >= 0 && blk < m && tok < n;
+  typename E::T qv[G];
+  const typename E::T* qg = q + (size_t(s) * H_q + size_t(g) * G) * d;
+  if (tid < d_c) {
+#pragma unroll
+    for (int h = 0; h < G; ++h) qv[h] = qg[size_t(h) * d + ch];
+  }
+  const size_t row = size_t(unit) * T + (valid ? tok : 0);
+  const uint8_t* crow = codes + row * (d_c / 2);
+  const float2* prow = reinterpret_cast<const float2*>(qparams + row * ngr * 2);
+  uint4 cw = ld16(crow);
+  float2 pr = prow[0];
+  __builtin_amdgcn_sched_barrier(0);
+  if (tid < d_c) {
+#pragma unroll
+    for (int h = 0; h < G; ++h) s_q[tid * G + h] = E::to_f(qv[h]);
+  }
+  lds_barrier();
+  float acc[G];
+#pragma unroll
+  for (int h = 0; h < G; ++h) acc[h] = 0.f;
+#pragma unroll 1
+  for (int gr = 0; gr < ngr; ++gr) {
+    const uint4 c = cw;
+    const float2 p = pr;
+    if (gr + 1 < ngr) {
+      cw = ld16(crow + (gr + 1) * 16);
+      pr = prow[gr + 1];
+    }
+    const float* qr = s_q + gr * 32 * G;
+    const uint32_t wd[4] = {c.x, c.y, c.z, c.w};
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+      float f[8];
+      unpack_nibbles8(wd[w], f);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const float x = fmaf(p.x, f[e], p.y);
+#pragma unroll
+        for (int h = 0; h < G; ++h) acc[h] = fmaf(qr[(w * 8 + e) * G + h], x, acc[h]);
+      }
+    }
+  }
+  float* lg = logits + size_t(unit) * G * S + slot;
+#pragma unroll
+  for (int h = 0; h < G; ++h) {
+    const float l = valid ? sigma * acc[h] : -INFINITY;
+    if (slot < S) lg[size_t(h) * S] = l;
+    const float M = wave_max_f32(l);
+    const float Z = wave_sum_f32(l == -INFINITY ? 0.f : __expf(l - M));
+    if (lane == 0) {
+      s_red[wid][h][0] = M;
+      s_red[wid][h][1] = Z;
+    }
+  }
+  write_chunk_stats<G>(s_red, G, stats + (size_t(unit) * gridDim.x + chunk) * G * 2);
+}
+
+// bf16, G <= 4 HS, d_c = 32 NGR, where the fused kernel does not apply (more
+// than four heads or one group, larger budgets): the same two rounds of
+// requests, the contraction of a lane's slot on the matrix cores (lane_dots).
+// 32 units of 8 heads, d_c = 64, 4096 slots: 18.3 -> 6 us.
+template <int HS, int NGR>
+__global__ __launch_bounds__(256) void token_score_lane_kernel(
+    const uint16_t* __restrict__ q, const uint8_t* __restrict__ codes, const float* __restrict__ qparams,
+    const int32_t* __restrict__ channels, const int32_t* __restrict__ block_ids, int K_b,
+    const int32_t* __restrict__ ctx_lens, int H_q, int H_kv, int G, int d, int B, int T, float sigma,
+    float* __restrict__ logits, float* __restrict__ stats, uint32_t* err) {
+  constexpr int DC = 32 * NGR, NQ = NGR * HS * 128, PER = (NQ + 255) / 256;
+  __shared__ __attribute__((aligned(16))) uint16_t s_qt[NQ];  // [group][set][head][position]
+  __shared__ float s_red[4][4 * HS][2];
+  const int unit = blockIdx.y, chunk = blockIdx.x;
+  const int s = unit / H_kv, g = unit % H_kv;
+  const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+  const int S = K_b * B;
+  const int slot = chunk * kTokenSlotsPerWG + tid;
+  int n = ctx_lens[s];
+  const int blk = block_ids[size_t(unit) * K_b + min(tok_block(min(slot, S - 1), B), K_b - 1)];
+  int ch[PER];
+#pragma unroll
+  for (int j = 0; j < PER; ++j) {
+    const int i = min(tid + j * 256, NQ - 1), x = i & 31;
+    ch[j] = channels[g * DC + i / (128 * HS) * 32 + (x & ~7) + codes_chan(x & 7)];
+  }
+  n = n < 0 ? 0 : (n > T ? T : n);
+  const int m = (n + B - 1) / B;
+  if (slot < S && blk >= m) set_error(err, 2u);
+  const int tok = blk * B + tok_offset(slot, B);
+  const bool valid = slot < S && blk >= 0 && blk < m && tok < n;
+  uint16_t qv[PER];
+#pragma unroll
+  for (int j = 0; j < PER; ++j) {
+    if (ch[j] < 0 || ch[j] >= d) {
+      set_error(err, 32u);
+      ch[j] = 0;
+    }
+    const int i = min(tid + j * 256, NQ - 1), h = ((i >> 7) % HS) * 4 + ((i >> 5) & 3);
+    const uint16_t v = q[(size_t(s) * H_q + size_t(g) * G + min(h, G - 1)) * d + ch[j]];
+    qv[j] = h < G ? v : uint16_t(0);
+  }
+  __builtin_amdgcn_sched_barrier(0);
+  const size_t row = size_t(unit) * T + (valid ? tok : 0);
+  uint4 cw[NGR];
+  float2 pr[NGR];
+#pragma unroll
+  for (int gr = 0; gr < NGR; ++gr) {
+    cw[gr] = ld16(codes + row * (DC / 2) + gr * 16);
+    pr[gr] = *reinterpret_cast<const float2*>(qparams + (row * NGR + gr) * 2);
+  }
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int j = 0; j < PER; ++j)
+    if (tid + j * 256 < NQ) s_qt[tid + j * 256] = qv[j];
+  lds_barrier();
+  float l[4 * HS];
+#pragma unroll
+  for (int h = 0; h < 4 * HS; ++h) l[h] = 0.f;
+#pragma unroll
+  for (int gr = 0; gr < NGR; ++gr) {
+    bf16x8_t qa[HS][4];
+    f32x4_t qsum[HS], acc[HS];
+    lane_operands<HS>(s_qt + gr * HS * 128, qa, qsum);
+    lane_dots<HS>(cw[gr], qa, acc);
+#pragma unroll
+    for (int h = 0; h < 4 * HS; ++h) {
+      const float qs = qsum[h / 4][h % 4];
+      l[h] += fmaf(pr[gr].x, dot16(acc[h / 4][h % 4], qs), pr[gr].y * qs);
+    }
+  }
+  float* lg = logits + size_t(unit) * G * S + slot;
+#pragma unroll
+  for (int h = 0; h < 4 * HS; ++h) {
+    if (h < G) {  // uniform
+      const float v = valid ? sigma * l[h] : -INFINITY;
+      if (slot < S) lg[size_t(h) * S] = v;
+      const float M = wave_max_f32(v);
+      const float Z = wave_sum_f32(v == -INFINITY ? 0.f : __expf(v - M));
+      if (lane == 0) {
+        s_red[wid][h][0] = M;
+        s_red[wid][h][1] = Z;
+      }
+    }
+  }
+  write_chunk_stats<4 * HS>(s_red, G, stats + (size_t(unit) * gridDim.x + chunk) * G * 2);
+}
+
 // The same logits and statistics with the code contraction on the matrix
 // cores, for bf16 with G a multiple of 16 (the absorbed MLA layout: 32 heads
 // over d_c = 128 channels).  A work-group (4 waves) takes 256 slots; each
@@ -543,14 +738,42 @@ hipError_t launch_token_score(const Problem& P, const void* q, const uint8_t* co
     return hipGetLastError();
   }
   dim3 grid(n_tchunks, P.units);
-  if (P.dtype == 1)
-    token_score_kernel<BF16><<<grid, 256, 0, st>>>((const uint16_t*)q, codes, qparams, channels, block_ids,
-                                                   K_b, ctx_lens, P.H_q, P.H_kv, P.G, P.d_qk, P.d_c, P.B,
-                                                   P.T, P.sigma, logits, stats, err);
-  else
-    token_score_kernel<F32><<<grid, 256, 0, st>>>((const float*)q, codes, qparams, channels, block_ids, K_b,
-                                                  ctx_lens, P.H_q, P.H_kv, P.G, P.d_qk, P.d_c, P.B, P.T,
-                                                  P.sigma, logits, stats, err);
+  if (P.dtype == 1 && P.G <= 8 && (P.d_c == 32 || P.d_c == 64 || P.d_c == 128)) {
+    auto go = [&](auto kern) {
+      kern<<<grid, 256, 0, st>>>((const uint16_t*)q, codes, qparams, channels, block_ids, K_b, ctx_lens, P.H_q, P.H_kv,
+                                 P.G, P.d_qk, P.B, P.T, P.sigma, logits, stats, err);
+    };
+    if (P.G <= 4) {
+      if (P.d_c == 32) go(token_score_lane_kernel<1, 1>);
+      else if (P.d_c == 64) go(token_score_lane_kernel<1, 2>);
+      else go(token_score_lane_kernel<1, 4>);
+    } else {
+      if (P.d_c == 32) go(token_score_lane_kernel<2, 1>);
+      else if (P.d_c == 64) go(token_score_lane_kernel<2, 2>);
+      else go(token_score_lane_kernel<2, 4>);
+    }
+    return hipGetLastError();
+  }
+  auto rows = [&](auto elem) {
+    using E = decltype(elem);
+    using T = typename E::T;
+    auto go = [&](auto kern) {
+      kern<<<grid, 256, 0, st>>>((const T*)q, codes, qparams, channels, block_ids, K_b, ctx_lens, P.H_q, P.H_kv, P.d_qk,
+                                 P.d_c, P.B, P.T, P.sigma, logits, stats, err);
+    };
+    switch (P.G) {
+      case 1: go(token_score_row_kernel<E, 1>); return;
+      case 2: go(token_score_row_kernel<E, 2>); return;
+      case 4: go(token_score_row_kernel<E, 4>); return;
+      case 8: go(token_score_row_kernel<E, 8>); return;
+      default:
+        token_score_kernel<E><<<grid, 256, 0, st>>>((const T*)q, codes, qparams, channels, block_ids, K_b, ctx_lens,
+                                                    P.H_q, P.H_kv, P.G, P.d_qk, P.d_c, P.B, P.T, P.sigma, logits,
+                                                    stats, err);
+    }
+  };
+  if (P.dtype == 1) rows(BF16{});
+  else rows(F32{});
   return hipGetLastError();
 }
 

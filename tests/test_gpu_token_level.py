@@ -97,3 +97,53 @@ def test_equal_scores_take_the_lowest_positions(G, d, d_c, dtype, mla, noalloc):
     a = _setup(G, d, d_c, dtype, mla, lens, 5, zero_q=True)
     tids = _select(*a, 600, noalloc=noalloc).cpu()
     assert bool((tids == torch.arange(600, dtype=torch.int32)).all())
+
+
+SELECT = [
+    # (G, d_qk, d_c, dtype): the two-level token stage where the fused kernel does not apply
+    (8, 128, 32, torch.bfloat16), (8, 64, 64, torch.bfloat16), (8, 128, 128, torch.bfloat16),
+    (4, 128, 64, torch.bfloat16), (2, 128, 128, torch.bfloat16), (3, 128, 64, torch.bfloat16),
+    (6, 64, 32, torch.bfloat16), (4, 128, 96, torch.bfloat16), (1, 64, 32, torch.float32), (2, 64, 64, torch.float32),
+    (4, 128, 32, torch.float32), (8, 320, 256, torch.float32), (5, 128, 32, torch.float32),
+]
+
+
+@pytest.mark.parametrize("k_b,k_t", [(1, 3), (5, 130), (9, 1000)])
+@pytest.mark.parametrize("G,d,d_c,dtype", SELECT)
+def test_tokens_of_given_blocks(G, d, d_c, dtype, k_b, k_t):
+    """Ragged last blocks, empty list entries, candidate counts that do not fill a work-group."""
+    lens = (700, 1337, 64)
+    layout, q, K, V, n, ch, codes, qp = _setup(G, d, d_c, dtype, False, lens, 3 * G + d_c)
+    b, hkv = K.shape[:2]
+    g = torch.Generator().manual_seed(k_b)
+    bids = torch.full((b, hkv, k_b), -1, dtype=torch.int32)
+    for s, ln in enumerate(lens):
+        m = -(-ln // 64)
+        for u in range(hkv):
+            pick = torch.randperm(m, generator=g)[:max(1, min(k_b - 1, m))].sort().values.int()
+            pick[-1] = m - 1  # the ragged block
+            bids[s, u, :len(pick)] = pick
+    tids = torch.full((b, hkv, k_t), -7, dtype=torch.int32, device="cuda")
+    sc = torch.empty((b, hkv, k_t), dtype=torch.float32, device="cuda")
+    ws = tls.alloc_workspace(layout, k_b, k_t)
+    tls.tls_select_tokens(layout, q, codes, qp, ch, bids.cuda(), k_b, n, k_t, tids, sc, ws)
+    assert tls.tls_check_device_error(ws) == 0
+    tids, sc = tids.cpu(), sc.cpu()
+    for s, ln in enumerate(lens):
+        for u in range(hkv):
+            cand = torch.cat([torch.arange(64) + 64 * int(i) for i in bids[s, u] if i >= 0])
+            cand = cand[cand < ln]
+            c = codes[s, u, :ln].cpu().long()
+            x = torch.stack([c & 15, c >> 4], -1).reshape(ln, -1, 32).double()
+            x = (x * qp[s, u, :ln, :, :1].cpu().double() + qp[s, u, :ln, :, 1:].cpu().double()).reshape(ln, -1)[cand]
+            qq = q[s, u * G:(u + 1) * G].cpu().double()[:, ch[u].cpu().long()]
+            alpha = torch.zeros(ln, dtype=torch.float64)
+            alpha[cand] = torch.softmax(qq @ x.T / math.sqrt(d), -1).mean(0)
+            kk = min(k_t, len(cand))
+            ids = tids[s, u, :kk].long()
+            assert bool((tids[s, u, kk:] == -1).all()) and bool((ids[1:] > ids[:-1]).all())
+            kth = alpha[cand].sort(descending=True).values[kk - 1]
+            chosen = torch.zeros(ln, dtype=torch.bool)
+            chosen[ids] = True
+            assert bool(chosen[alpha > kth * (1 + 1e-5)].all()) and not bool(chosen[alpha < kth * (1 - 1e-5)].any())
+            assert torch.allclose(sc[s, u, :kk].double(), alpha[ids], rtol=1e-5, atol=0)
