@@ -284,8 +284,8 @@ hipError_t launch_attention_mla_mfma(const Problem& P, const void* q, const KvVi
                                      const int32_t* ctx_lens, int K_t, int nsplit, float* po, float* plse,
                                      uint32_t* err, hipStream_t st);
 hipError_t launch_attention_gqa(const Problem& P, const void* q, const KvView& kv, const TokenList& tl,
-                                const int32_t* ctx_lens, int K_t, int nsplit, float* po, float* plse,
-                                uint32_t* err, hipStream_t st);
+                                const int32_t* ctx_lens, int K_t, int nsplit, const SplitOut& so, uint32_t* err,
+                                hipStream_t st, bool* merged);
 
 int attn_tokens_per_split(const Problem& P) {
   if (P.mla) return mla_mfma_ok(P) ? mla_mfma_tokens_per_split() : kMlaCt;
@@ -318,19 +318,20 @@ int attn_splits_for(const Problem& P, int K_t, int requested) {
 }
 
 hipError_t launch_attention(const Problem& P, const void* q, const KvView& kv, const TokenList& tl,
-                            const int32_t* ctx_lens, int K_t, int nsplit, float* po, float* plse,
-                            uint32_t* err, hipStream_t st) {
+                            const int32_t* ctx_lens, int K_t, int nsplit, const SplitOut& so, uint32_t* err,
+                            hipStream_t st, bool* merged) {
+  *merged = false;
   if (P.mla && mla_mfma_ok(P))
-    return launch_attention_mla_mfma(P, q, kv, tl, ctx_lens, K_t, nsplit, po, plse, err, st);
+    return launch_attention_mla_mfma(P, q, kv, tl, ctx_lens, K_t, nsplit, so.po, so.plse, err, st);
   if (P.mla) {
     dim3 grid(nsplit, P.units);
     const int ct = (K_t + nsplit - 1) / nsplit;
     attn_mla_kernel<<<grid, 256, 0, st>>>((const uint16_t*)q, (const uint16_t*)kv.k, kv.slot_map, kv.n_slots,
                                           tl, ctx_lens, P.H_q, P.H_kv, P.G, P.d_qk, P.d_v, P.T, P.B,
-                                          P.m_max, K_t, ct, P.sigma, po, plse, err);
+                                          P.m_max, K_t, ct, P.sigma, so.po, so.plse, err);
     return hipGetLastError();
   }
-  return launch_attention_gqa(P, q, kv, tl, ctx_lens, K_t, nsplit, po, plse, err, st);
+  return launch_attention_gqa(P, q, kv, tl, ctx_lens, K_t, nsplit, so, err, st, merged);
 }
 
 hipError_t launch_merge(const Problem& P, const float* po, const float* plse, int nsplit, void* out, float* lse,

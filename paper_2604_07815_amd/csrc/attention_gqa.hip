@@ -27,8 +27,7 @@ __device__ __forceinline__ void attn_gqa_body(
     const typename E::T* __restrict__ q, const typename E::T* __restrict__ Kp,
     const typename E::T* __restrict__ Vp, const int32_t* __restrict__ slot_map, int64_t n_slots,
     const TokenList& tl, const int32_t* __restrict__ ctx_lens, int H_q, int H_kv, int T,
-    int B, int m_max, int K_t, int tpw, float sigma, float* __restrict__ po, float* __restrict__ plse,
-    uint32_t* err) {
+    int B, int m_max, int K_t, int tpw, float sigma, const SplitOut& so, uint32_t* err) {
   using S = typename E::T;
   constexpr int V = E::kVec;                // elements per 16-byte piece
   constexpr int ROWB = D * int(sizeof(S));  // bytes per K or V row
@@ -224,8 +223,13 @@ __device__ __forceinline__ void attn_gqa_body(
     const int h = idx / D;
     const float o = (s_acc[idx] + s_acc[G * D + idx]) + (s_acc[2 * G * D + idx] + s_acc[3 * G * D + idx]);
     const float L = s_l[h];
-    po[pbase * D + idx] = L > 0.f ? o / L : 0.f;
-    if (idx % D == 0) plse[pbase + h] = L > 0.f ? s_m[h] + logf(L) : -INFINITY;
+    store_partial(so, so.po + pbase * D + idx, L > 0.f ? o / L : 0.f);
+    if (idx % D == 0) store_partial(so, so.plse + pbase + h, L > 0.f ? s_m[h] + logf(L) : -INFINITY);
+  }
+  if constexpr (NCH == 1) {
+    static_assert(CT * ROWB >= (G * kMaxSplits + 1) * 4, "merge scratch fits in the V buffer");
+    if (so.arrive)
+      arrive_and_merge<E, 256, D>(so, unit, nsplit, G, size_t(s) * H_q + size_t(g) * G, reinterpret_cast<uint32_t*>(sV0));
   }
 }
 
@@ -237,7 +241,7 @@ __global__ __launch_bounds__(256) void attn_gqa_kernel(
     int B, int m_max, int K_t, int tpw, float sigma, float* __restrict__ po, float* __restrict__ plse,
     uint32_t* err) {
   attn_gqa_body<E, D, G, kAttnMaxTPW / kAttnCT>(q, Kp, Vp, slot_map, n_slots, tl, ctx_lens, H_q, H_kv, T, B, m_max, K_t,
-                                                tpw, sigma, po, plse, err);
+                                                tpw, sigma, SplitOut{po, plse, nullptr, nullptr, nullptr}, err);
 }
 
 // Work-groups of one chunk (small budgets, or few units cut into many splits):
@@ -248,10 +252,8 @@ __global__ __launch_bounds__(256) void attn_gqa_chunk_kernel(
     const typename E::T* __restrict__ q, const typename E::T* __restrict__ Kp,
     const typename E::T* __restrict__ Vp, const int32_t* __restrict__ slot_map, int64_t n_slots,
     const TokenList tl, const int32_t* __restrict__ ctx_lens, int H_q, int H_kv, int T,
-    int B, int m_max, int K_t, int tpw, float sigma, float* __restrict__ po, float* __restrict__ plse,
-    uint32_t* err) {
-  attn_gqa_body<E, D, G, 1>(q, Kp, Vp, slot_map, n_slots, tl, ctx_lens, H_q, H_kv, T, B, m_max, K_t, tpw, sigma, po,
-                            plse, err);
+    int B, int m_max, int K_t, int tpw, float sigma, const SplitOut so, uint32_t* err) {
+  attn_gqa_body<E, D, G, 1>(q, Kp, Vp, slot_map, n_slots, tl, ctx_lens, H_q, H_kv, T, B, m_max, K_t, tpw, sigma, so, err);
 }
 
 template <int D, int G, int NW, int TPWV, bool WHOLE>
@@ -259,12 +261,10 @@ __global__ __launch_bounds__(64 * NW) void attn_gqa_mfma_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ Kp, const uint16_t* __restrict__ Vp,
     const int32_t* __restrict__ slot_map, int64_t n_slots, const TokenList tl,
     const int32_t* __restrict__ ctx_lens, int H_q, int H_kv, int T, int B, int m_max, int K_t, int tpw,
-    float sigma, float* __restrict__ po, float* __restrict__ plse, uint16_t* __restrict__ out,
-    float* __restrict__ lse, uint32_t* err) {
+    float sigma, const SplitOut so, uint32_t* err) {
   __shared__ AttnGqaLds<D, NW, TPWV> lds;
   attn_gqa_mfma_body<D, G, NW, TPWV, WHOLE>(lds, q, Kp, Vp, slot_map, n_slots, tl, ctx_lens, H_q, H_kv, T, B, m_max,
-                                            K_t, tpw, sigma, po, plse, out, lse, err, blockIdx.y, blockIdx.x,
-                                            gridDim.x);
+                                            K_t, tpw, sigma, so, err, blockIdx.y, blockIdx.x, gridDim.x);
 }
 
 bool gqa_whole_ok(const Problem& P, int K_t);
@@ -295,6 +295,15 @@ static int mfma_wgs_per_cu_g(int G) {
     default: return mfma_wgs_per_cu<D, 8>();
   }
 }
+
+// The unit's last work-group merges the splits where a thread of it has one
+// pair of output columns and the partials are no more than a work-group reads
+// in the time of a launch.  Against the merge kernel (whole step, 8 to 248
+// units, 256 to 2048 tokens, D = 64 and 128): 0.8 to 1.8 us less with 1, 2 and
+// 4 heads (b = 1, 48k: 33.4 -> 32.1 us) and 8 heads of 64; with 8 heads of 128
+// between 1.2 less and 1.0 more, so those keep the kernel.
+constexpr int kFoldColumns = 512;
+constexpr long kFoldFloats = 32768;
 
 constexpr int kWideMinTokens = 768;  // tokens per 12-wave split work-group worth its prologue
 
@@ -346,47 +355,55 @@ int gqa_auto_splits(const Problem& P, int K_t) {
   return best;
 }
 
+// Returns whether the kernel merges the splits itself.
 template <class E, int D, int G>
-static void launch_t(const Problem& P, const void* q, const KvView& kv, const TokenList& tl,
-                     const int32_t* ctx_lens, int K_t, int nsplit, float* po, float* plse, uint32_t* err,
+static bool launch_t(const Problem& P, const void* q, const KvView& kv, const TokenList& tl,
+                     const int32_t* ctx_lens, int K_t, int nsplit, const SplitOut& so_in, uint32_t* err,
                      hipStream_t st) {
   using S = typename E::T;
   dim3 grid(nsplit, P.units);
   int tpw = (K_t + nsplit - 1) / nsplit;
+  SplitOut so = so_in;
+  if (G * D > kFoldColumns || long(nsplit) * G * D > kFoldFloats) so.arrive = nullptr;
   if constexpr (E::kIsBf16) {
     if (gqa_use_wide(P, K_t, nsplit, device_cus())) {
       constexpr int wstep = 16 * kWholeNW;
       tpw = (tpw + wstep - 1) / wstep * wstep;
       attn_gqa_mfma_kernel<D, G, kWholeNW, kWholeTPWV, false><<<grid, 64 * kWholeNW, 0, st>>>(
           (const uint16_t*)q, (const uint16_t*)kv.k, (const uint16_t*)kv.v, kv.slot_map, kv.n_slots, tl, ctx_lens,
-          P.H_q, P.H_kv, P.T, P.B, P.m_max, K_t, tpw, P.sigma, po, plse, nullptr, nullptr, err);
-      return;
+          P.H_q, P.H_kv, P.T, P.B, P.m_max, K_t, tpw, P.sigma, so, err);
+      return so.arrive != nullptr;
     }
     constexpr int step = 16 * kAttnNW;  // whole tiles for every wave
     tpw = (tpw + step - 1) / step * step;
     attn_gqa_mfma_kernel<D, G, kAttnNW, kAttnMaxTPWBf16 / kAttnNW, false><<<grid, 64 * kAttnNW, 0, st>>>(
         (const uint16_t*)q, (const uint16_t*)kv.k, (const uint16_t*)kv.v, kv.slot_map, kv.n_slots, tl,
-        ctx_lens, P.H_q, P.H_kv, P.T, P.B, P.m_max, K_t, tpw, P.sigma, po, plse, nullptr, nullptr, err);
+        ctx_lens, P.H_q, P.H_kv, P.T, P.B, P.m_max, K_t, tpw, P.sigma, so, err);
+    return so.arrive != nullptr;
   } else {
     tpw = (tpw + kAttnCT - 1) / kAttnCT * kAttnCT;
-    auto go = [&](auto kern) {
-      kern<<<grid, 256, 0, st>>>((const S*)q, (const S*)kv.k, (const S*)kv.v, kv.slot_map, kv.n_slots, tl, ctx_lens,
-                                 P.H_q, P.H_kv, P.T, P.B, P.m_max, K_t, tpw, P.sigma, po, plse, err);
-    };
-    if (tpw == kAttnCT) go(attn_gqa_chunk_kernel<E, D, G>);
-    else go(attn_gqa_kernel<E, D, G>);
+    if (tpw == kAttnCT) {
+      attn_gqa_chunk_kernel<E, D, G><<<grid, 256, 0, st>>>((const S*)q, (const S*)kv.k, (const S*)kv.v, kv.slot_map,
+                                                           kv.n_slots, tl, ctx_lens, P.H_q, P.H_kv, P.T, P.B, P.m_max,
+                                                           K_t, tpw, P.sigma, so, err);
+      return so.arrive != nullptr;
+    }
+    attn_gqa_kernel<E, D, G><<<grid, 256, 0, st>>>((const S*)q, (const S*)kv.k, (const S*)kv.v, kv.slot_map,
+                                                   kv.n_slots, tl, ctx_lens, P.H_q, P.H_kv, P.T, P.B,
+                                                   P.m_max, K_t, tpw, P.sigma, so.po, so.plse, err);
+    return false;
   }
 }
 
 template <class E, int D>
 static bool launch_d(const Problem& P, const void* q, const KvView& kv, const TokenList& tl,
-                     const int32_t* ctx_lens, int K_t, int nsplit, float* po, float* plse, uint32_t* err,
-                     hipStream_t st) {
+                     const int32_t* ctx_lens, int K_t, int nsplit, const SplitOut& so, uint32_t* err, hipStream_t st,
+                     bool* merged) {
   switch (P.G) {
-    case 1: launch_t<E, D, 1>(P, q, kv, tl, ctx_lens, K_t, nsplit, po, plse, err, st); return true;
-    case 2: launch_t<E, D, 2>(P, q, kv, tl, ctx_lens, K_t, nsplit, po, plse, err, st); return true;
-    case 4: launch_t<E, D, 4>(P, q, kv, tl, ctx_lens, K_t, nsplit, po, plse, err, st); return true;
-    case 8: launch_t<E, D, 8>(P, q, kv, tl, ctx_lens, K_t, nsplit, po, plse, err, st); return true;
+    case 1: *merged = launch_t<E, D, 1>(P, q, kv, tl, ctx_lens, K_t, nsplit, so, err, st); return true;
+    case 2: *merged = launch_t<E, D, 2>(P, q, kv, tl, ctx_lens, K_t, nsplit, so, err, st); return true;
+    case 4: *merged = launch_t<E, D, 4>(P, q, kv, tl, ctx_lens, K_t, nsplit, so, err, st); return true;
+    case 8: *merged = launch_t<E, D, 8>(P, q, kv, tl, ctx_lens, K_t, nsplit, so, err, st); return true;
     default: return false;
   }
 }
@@ -405,7 +422,7 @@ static void launch_whole_t(const Problem& P, const void* q, const KvView& kv, co
   const int tpw = (K_t + step - 1) / step * step;
   attn_gqa_mfma_kernel<D, G, kWholeNW, kWholeTPWV, true><<<dim3(1, P.units), 64 * kWholeNW, 0, st>>>(
       (const uint16_t*)q, (const uint16_t*)kv.k, (const uint16_t*)kv.v, kv.slot_map, kv.n_slots, tl,
-      ctx_lens, P.H_q, P.H_kv, P.T, P.B, P.m_max, K_t, tpw, P.sigma, nullptr, nullptr, (uint16_t*)out, lse, err);
+      ctx_lens, P.H_q, P.H_kv, P.T, P.B, P.m_max, K_t, tpw, P.sigma, SplitOut{nullptr, nullptr, nullptr, out, lse}, err);
 }
 
 template <int D>
@@ -429,15 +446,15 @@ hipError_t launch_attention_gqa_whole(const Problem& P, const void* q, const KvV
 }
 
 hipError_t launch_attention_gqa(const Problem& P, const void* q, const KvView& kv, const TokenList& tl,
-                                const int32_t* ctx_lens, int K_t, int nsplit, float* po, float* plse,
-                                uint32_t* err, hipStream_t st) {
+                                const int32_t* ctx_lens, int K_t, int nsplit, const SplitOut& so, uint32_t* err,
+                                hipStream_t st, bool* merged) {
   bool ok = false;
   if (P.dtype == 1) {
-    if (P.d_qk == 128) ok = launch_d<BF16, 128>(P, q, kv, tl, ctx_lens, K_t, nsplit, po, plse, err, st);
-    else if (P.d_qk == 64) ok = launch_d<BF16, 64>(P, q, kv, tl, ctx_lens, K_t, nsplit, po, plse, err, st);
+    if (P.d_qk == 128) ok = launch_d<BF16, 128>(P, q, kv, tl, ctx_lens, K_t, nsplit, so, err, st, merged);
+    else if (P.d_qk == 64) ok = launch_d<BF16, 64>(P, q, kv, tl, ctx_lens, K_t, nsplit, so, err, st, merged);
   } else {
-    if (P.d_qk == 128) ok = launch_d<F32, 128>(P, q, kv, tl, ctx_lens, K_t, nsplit, po, plse, err, st);
-    else if (P.d_qk == 64) ok = launch_d<F32, 64>(P, q, kv, tl, ctx_lens, K_t, nsplit, po, plse, err, st);
+    if (P.d_qk == 128) ok = launch_d<F32, 128>(P, q, kv, tl, ctx_lens, K_t, nsplit, so, err, st, merged);
+    else if (P.d_qk == 64) ok = launch_d<F32, 64>(P, q, kv, tl, ctx_lens, K_t, nsplit, so, err, st, merged);
   }
   if (!ok) return hipErrorInvalidValue;
   return hipGetLastError();

@@ -105,6 +105,136 @@ __device__ inline short bf16_bits_rne(float f) {
 
 __device__ inline float exp_or_zero(float x) { return x == -INFINITY ? 0.f : expf(x); }
 
+// ---------------------------------------------------------------------------
+// Split merge by a unit's last work-group, without a launch of its own.
+//
+// The work-groups of a unit store their partials and count themselves in; the
+// last one reads them all and writes the output.  They may run on different
+// XCDs, whose L2 caches are not coherent for ordinary accesses, and a device
+// fence would write back and invalidate a whole L2 (measured: 4 times the
+// attention's time).  So the partials themselves are relaxed agent-scope
+// atomics, 4 bytes a store and 8 a load, which go past the L2s to memory: a
+// wave waits for its stores (vmcnt), the work-group meets at a barrier, and
+// only then the count is raised; the last arrival's loads are issued after its
+// count came back.  The count is cleared by the kernel that chose the tokens,
+// earlier in the same call.
+// ---------------------------------------------------------------------------
+struct SplitOut {
+  float* po;         // [units][nsplit][G][D]
+  float* plse;       // [units][nsplit][G]
+  uint32_t* arrive;  // [units] arrivals, or NULL: merge_kernel combines the partials
+  void* out;         // used with arrive
+  float* lse;
+};
+
+__device__ inline void store_partial(const SplitOut& so, float* p, float v) {
+  if (so.arrive) __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  else *p = v;
+}
+__device__ inline float2 load_partial2(const float* p) {
+  const uint64_t u = __hip_atomic_load(reinterpret_cast<const uint64_t*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  return make_float2(__uint_as_float(uint32_t(u)), __uint_as_float(uint32_t(u >> 32)));
+}
+
+// Called by all NT threads of a work-group after its partials' stores;
+// `scratch`: G * kMaxSplits + 1 words of LDS that nothing else uses any more.
+// Output rows of the unit start at orow.
+template <class E, int NT, int D>
+__device__ inline void arrive_and_merge(const SplitOut& so, int unit, int nsplit, int G, size_t orow,
+                                        uint32_t* scratch) {
+  constexpr int NW = NT / 64;
+  const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+  asm volatile("s_waitcnt vmcnt(0)" : : : "memory");  // this wave's partials are in memory
+  __syncthreads();
+  if (tid == 0) scratch[0] = __hip_atomic_fetch_add(so.arrive + unit, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __syncthreads();
+  if (scratch[0] != uint32_t(nsplit - 1)) return;  // uniform
+  asm volatile("" : : : "memory");
+  // split weights e^{lse_i - M} / sum_j e^{lse_j - M}; lane l holds splits l, l + 64
+  float* s_w = reinterpret_cast<float*>(scratch) + 1;  // [G][nsplit]
+  const float* ls = so.plse + size_t(unit) * nsplit * G;
+  for (int h = wid; h < G; h += NW) {
+    constexpr int PER = kMaxSplits / 64;
+    float l[PER], lm = -INFINITY;
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+      const int i = lane + 64 * j;
+      l[j] = i < nsplit ? __hip_atomic_load(ls + size_t(i) * G + h, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : -INFINITY;
+      lm = fmaxf(lm, l[j]);
+    }
+    const float M = wave_max_f32(lm);
+    float e[PER], es = 0.f;
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+      e[j] = M == -INFINITY ? 0.f : exp_or_zero(l[j] - M);
+      es += e[j];
+    }
+    const float W = wave_sum_f32(es);
+#pragma unroll
+    for (int j = 0; j < PER; ++j)
+      if (lane + 64 * j < nsplit) s_w[h * nsplit + lane + 64 * j] = W > 0.f ? e[j] / W : 0.f;
+    if (lane == 0 && so.lse) so.lse[orow + h] = W > 0.f ? M + logf(W) : -INFINITY;
+  }
+  __syncthreads();
+  const float* base = so.po + size_t(unit) * nsplit * G * D;
+  const size_t stride = size_t(G) * D;
+  // summed in merge_kernel's order, so that both give the same bits: with
+  // eight or more splits split i belongs to partial sum i % ROWS, with fewer
+  // to i % 4 (the ones past the last four to 0)
+  constexpr int ROWS = 256 / (D / 4), U = ROWS > 8 ? ROWS : 16;  // U partials in flight
+  static_assert(U % ROWS == 0, "partial sums per batch");
+  for (int x = 2 * tid; x < G * D; x += 2 * NT) {
+    const float* w = s_w + x / D * nsplit;
+    float o0 = 0.f, o1 = 0.f;
+    if (nsplit >= 8) {
+      float2 acc[ROWS];
+#pragma unroll
+      for (int r = 0; r < ROWS; ++r) acc[r] = make_float2(0.f, 0.f);
+      for (int i0 = 0; i0 < nsplit; i0 += U) {
+        float2 v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[u] = load_partial2(base + size_t(min(i0 + u, nsplit - 1)) * stride + x);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const bool in = i0 + u < nsplit;
+          const float wu = in ? w[i0 + u] : 0.f;
+          acc[u % ROWS].x = fmaf(wu, in ? v[u].x : 0.f, acc[u % ROWS].x);
+          acc[u % ROWS].y = fmaf(wu, in ? v[u].y : 0.f, acc[u % ROWS].y);
+        }
+      }
+      o0 = acc[0].x;
+      o1 = acc[0].y;
+#pragma unroll
+      for (int r = 1; r < ROWS; ++r) {
+        o0 += acc[r].x;
+        o1 += acc[r].y;
+      }
+    } else {
+      float2 v[8], acc[4];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) v[i] = load_partial2(base + size_t(min(i, nsplit - 1)) * stride + x);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) acc[r] = make_float2(0.f, 0.f);
+#pragma unroll
+      for (int i = 0; i < 7; ++i) {
+        if (i < nsplit) {
+          const int r = i < (nsplit & ~3) ? i % 4 : 0;
+#pragma unroll
+          for (int k = 0; k < 4; ++k) {
+            acc[k].x = k == r ? fmaf(w[i], v[i].x, acc[k].x) : acc[k].x;
+            acc[k].y = k == r ? fmaf(w[i], v[i].y, acc[k].y) : acc[k].y;
+          }
+        }
+      }
+      o0 = (acc[0].x + acc[1].x) + (acc[2].x + acc[3].x);
+      o1 = (acc[0].y + acc[1].y) + (acc[2].y + acc[3].y);
+    }
+    typename E::T* o = static_cast<typename E::T*>(so.out) + orow * D + x;
+    store_out<E>(o, o0);
+    store_out<E>(o + 1, o1);
+  }
+}
+
 // Transposing butterfly all-reduce over the MASK*2 lanes of a lane group:
 // while more than one value is left, each xor step sends half of the values
 // to the partner lane and keeps the other half, so NV values are reduced with

@@ -31,7 +31,8 @@ constexpr int kWholeTPWV = 176;  // tokens per wave in that mode: K_t <= 12 * 17
 //     column-wise straight from the row-major tile by ds_read_b64_tr_b16.
 // At the end the waves' (max, sum, accumulator) triples are merged in LDS.
 // Split mode (WHOLE = false): the work-group writes one normalised partial
-// and its log-sum-exp for the merge kernel.  Whole-unit mode (WHOLE = true,
+// and its log-sum-exp; the unit's last work-group merges them (or the merge
+// kernel, see SplitOut).  Whole-unit mode (WHOLE = true,
 // one work-group of 12 waves per unit, grid.x = 1): it writes the final
 // output row in the input dtype and the lse directly.
 // LDS of the body: per wave, one K tile and two V tiles of 16 rows, the
@@ -49,8 +50,7 @@ __device__ inline void attn_gqa_mfma_body(
     AttnGqaLds<D, NW, TPWV>& lds, const uint16_t* __restrict__ q, const uint16_t* __restrict__ Kp,
     const uint16_t* __restrict__ Vp, const int32_t* __restrict__ slot_map, int64_t n_slots, const TokenList tl,
     const int32_t* __restrict__ ctx_lens, int H_q, int H_kv, int T, int B, int m_max, int K_t, int tpw,
-    float sigma, float* __restrict__ po, float* __restrict__ plse, uint16_t* __restrict__ out,
-    float* __restrict__ lse, uint32_t* err, const int unit, const int split, const int nsplit) {
+    float sigma, const SplitOut& so, uint32_t* err, const int unit, const int split, const int nsplit) {
   constexpr int ROWB = D * 2;     // bytes per K or V row
   constexpr int LPR = ROWB / 16;  // 16-byte pieces per row
   constexpr int RPI = 64 / LPR;   // rows per wave-wide gather
@@ -287,12 +287,18 @@ __device__ inline void attn_gqa_mfma_body(
     const float lv = L > 0.f ? (M + __log2f(L)) * 0.6931471805599453f : -INFINITY;
     if constexpr (WHOLE) {
       const size_t row = size_t(s) * H_q + size_t(g) * G + h;
-      out[row * D + idx % D] = f32_to_bf16(L > 0.f ? o / L : 0.f);
-      if (lse && idx % D == 0) lse[row] = lv;
+      static_cast<uint16_t*>(so.out)[row * D + idx % D] = f32_to_bf16(L > 0.f ? o / L : 0.f);
+      if (so.lse && idx % D == 0) so.lse[row] = lv;
     } else {
-      po[pbase * D + idx] = L > 0.f ? o / L : 0.f;
-      if (idx % D == 0) plse[pbase + h] = lv;
+      store_partial(so, so.po + pbase * D + idx, L > 0.f ? o / L : 0.f);
+      if (idx % D == 0) store_partial(so, so.plse + pbase + h, lv);
     }
+  }
+  if constexpr (!WHOLE) {
+    static_assert(sizeof(lds.sK) >= (G * kMaxSplits + 1) * 4, "merge scratch fits in the K buffers");
+    if (so.arrive)
+      arrive_and_merge<BF16, NT, D>(so, unit, nsplit, G, size_t(s) * H_q + size_t(g) * G,
+                                 reinterpret_cast<uint32_t*>(&lds.sK[0][0]));
   }
 }
 

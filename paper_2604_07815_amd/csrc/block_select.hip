@@ -188,10 +188,11 @@ template <int EPT>
 __global__ __launch_bounds__(1024) void block_topk_kernel(const float* __restrict__ scores,
                                                           const int32_t* __restrict__ ctx_lens, int H_kv,
                                                           int T, int B, int m_max, int K_b,
-                                                          int32_t* __restrict__ block_ids) {
+                                                          int32_t* __restrict__ block_ids, uint32_t* arrive) {
   extern __shared__ uint32_t smem[];
   uint32_t* scratch = smem;
   const int unit = blockIdx.x;
+  if (arrive && threadIdx.x == 0) arrive[unit] = 0u;
   const int s = unit / H_kv;
   int n = ctx_lens[s];
   n = n < 0 ? 0 : (n > T ? T : n);
@@ -243,14 +244,13 @@ hipError_t launch_block_score(const Problem& P, const void* q, const void* kmax,
 }
 
 hipError_t launch_block_topk(const Problem& P, const float* scores, const int32_t* ctx_lens, int K_b,
-                             int32_t* block_ids, uint32_t* err, hipStream_t st) {
-  (void)err;
+                             int32_t* block_ids, uint32_t* arrive, hipStream_t st) {
   const size_t lds = size_t(topk_scratch_words(1024)) * sizeof(uint32_t);
   const int ept = (P.m_max + 1023) / 1024;
   auto go = [&](auto kern) {
     const hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(kern), lds);
     if (e != hipSuccess) return e;
-    kern<<<P.units, 1024, lds, st>>>(scores, ctx_lens, P.H_kv, P.T, P.B, P.m_max, K_b, block_ids);
+    kern<<<P.units, 1024, lds, st>>>(scores, ctx_lens, P.H_kv, P.T, P.B, P.m_max, K_b, block_ids, arrive);
     return hipGetLastError();
   };
   if (ept <= 1) return go(block_topk_kernel<1>);

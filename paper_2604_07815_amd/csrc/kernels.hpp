@@ -27,7 +27,7 @@ constexpr int kTokenSlotsPerWG = 256;
 
 // Workspace carving (byte offsets from the workspace base, 256-aligned).
 struct Workspace {
-  size_t err, xfer, qpn, bscores, bids, logits, stats, keys, kinfo, tids, po, plse, dkeys, dstats, dhist, total;
+  size_t err, xfer, qpn, bscores, bids, logits, stats, keys, kinfo, tids, po, plse, dkeys, dstats, dhist, arrive, total;
   int n_tchunks;  // token-score work-groups per unit
 };
 // Regions of the workspace, as a mask: a route of a call names the regions
@@ -41,7 +41,8 @@ enum : unsigned {
   kWsSplit = 32u,     // split-attention partials and their lse
   kWsDense = 64u,     // keys and statistics of the token-level operator
   kWsDenseHist = 128u,  // its key-bucket counts (optional: without them the keys are streamed once per radix pass)
-  kWsAll = 255u,
+  kWsArrive = 256u,   // split arrivals per unit (optional: without them a merge launch follows the attention)
+  kWsAll = 511u,
 };
 Workspace plan_workspace(const Problem& P, int K_b, int K_t, unsigned regions = kWsAll, int nsplit = kMaxSplits);
 
@@ -63,10 +64,12 @@ hipError_t launch_append_tokens(const Problem& P, const void* k_new, const void*
                                 float* qparams, void* pool_k, void* pool_v, const int32_t* slot_map, int64_t n_slots,
                                 uint32_t* err, hipStream_t st);
 
+// The selection launches below also clear the units' split arrivals (arrive,
+// nullable) for the attention that follows.
 hipError_t launch_block_score(const Problem& P, const void* q, const void* kmax, const void* kmin,
                               const int32_t* ctx_lens, float* qpn, float* scores, uint32_t* err, hipStream_t st);
 hipError_t launch_block_topk(const Problem& P, const float* scores, const int32_t* ctx_lens, int K_b,
-                             int32_t* block_ids, uint32_t* err, hipStream_t st);
+                             int32_t* block_ids, uint32_t* arrive, hipStream_t st);
 
 hipError_t launch_token_score(const Problem& P, const void* q, const uint8_t* codes, const float* qparams,
                               const int32_t* channels, const int32_t* block_ids, int K_b,
@@ -76,7 +79,7 @@ hipError_t launch_token_alpha(const Problem& P, const float* logits, const float
                               const int32_t* block_ids, int K_b, const int32_t* ctx_lens, uint32_t* keys, uint32_t* kinfo,
                               hipStream_t st);
 hipError_t launch_token_topk(const Problem& P, const uint32_t* keys, const uint32_t* kinfo, const int32_t* block_ids, int K_b,
-                             int K_t, int32_t* token_ids, float* token_scores, hipStream_t st);
+                             int K_t, int32_t* token_ids, float* token_scores, uint32_t* arrive, hipStream_t st);
 
 // One work-group per unit: (optional) block top-k from block_scores, then the
 // whole token selection on chip, over the selected blocks or, when
@@ -87,8 +90,8 @@ bool fused_token_select_ok(const Problem& P, int K_b, int K_t);
 hipError_t launch_token_select_fused(const Problem& P, const void* q, const uint8_t* codes, const float* qparams,
                                      const int32_t* channels, const float* block_scores,
                                      const int32_t* block_ids_in, int32_t* block_ids_out, const int32_t* ctx_lens,
-                                     int K_b, int K_t, int32_t* token_ids, float* token_scores, uint32_t* err,
-                                     hipStream_t st);
+                                     int K_b, int K_t, int32_t* token_ids, float* token_scores, uint32_t* arrive,
+                                     uint32_t* err, hipStream_t st);
 
 // Token-level selection over every valid token of each unit (the token-only
 // operator): alpha keys [units][T], per-chunk statistics and (nullable) key
@@ -98,8 +101,8 @@ size_t ds_stats_floats(const Problem& P);
 size_t ds_hist_words(const Problem& P);
 hipError_t launch_token_select_dense(const Problem& P, const void* q, const uint8_t* codes, const float* qparams,
                                      const int32_t* channels, const int32_t* ctx_lens, int K_t, float* stats,
-                                     uint32_t* keys, uint32_t* hist, int32_t* token_ids, uint32_t* err,
-                                     hipStream_t st);
+                                     uint32_t* keys, uint32_t* hist, int32_t* token_ids, uint32_t* arrive,
+                                     uint32_t* err, hipStream_t st);
 
 struct KvView {
   const void* k;
@@ -134,9 +137,12 @@ hipError_t launch_attention_gqa_whole(const Problem& P, const void* q, const KvV
                                       hipStream_t st);
 // K_t here is the number of list entries per unit (the budget for kListIds,
 // stride * B for kListBlocks, max_ctx for kListAll).
+// *merged: the splits are combined by the kernel itself (so.arrive given and
+// worth it), else launch_merge has to follow.
+struct SplitOut;  // attn_common.hpp
 hipError_t launch_attention(const Problem& P, const void* q, const KvView& kv, const TokenList& tl,
-                            const int32_t* ctx_lens, int K_t, int nsplit, float* po, float* plse,
-                            uint32_t* err, hipStream_t st);
+                            const int32_t* ctx_lens, int K_t, int nsplit, const SplitOut& so, uint32_t* err,
+                            hipStream_t st, bool* merged);
 hipError_t launch_merge(const Problem& P, const float* po, const float* plse, int nsplit, void* out,
                         float* lse, hipStream_t st);
 

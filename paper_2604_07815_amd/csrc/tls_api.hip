@@ -6,6 +6,7 @@
 #include <mutex>
 
 #include "tls.h"
+#include "attn_common.hpp"
 #include "kernels.hpp"
 
 using tls::Problem;
@@ -115,7 +116,7 @@ uint32_t* err_word(void* ws) { return static_cast<uint32_t*>(ws); }
 hipError_t run_token_select(const Problem& P, const tls::Workspace& W, const void* q, const uint8_t* codes,
                             const float* qparams, const int32_t* channels, const int32_t* block_ids, int K_b,
                             const int32_t* ctx_lens, int K_t, int32_t* token_ids, float* token_scores, void* ws,
-                            uint32_t* err, hipStream_t stream, hipEvent_t* ev) {
+                            uint32_t* arrive, uint32_t* err, hipStream_t stream, hipEvent_t* ev) {
   hipError_t e = tls::launch_token_score(P, q, codes, qparams, channels, block_ids, K_b, ctx_lens,
                                          at<float>(ws, W.logits), at<float>(ws, W.stats), W.n_tchunks, err, stream);
   if (e != hipSuccess) return e;
@@ -125,7 +126,7 @@ hipError_t run_token_select(const Problem& P, const tls::Workspace& W, const voi
   if (e != hipSuccess) return e;
   if (ev) (void)hipEventRecord(ev[1], stream);
   return tls::launch_token_topk(P, at<uint32_t>(ws, W.keys), at<uint32_t>(ws, W.kinfo), block_ids, K_b, K_t,
-                                token_ids, token_scores, stream);
+                                token_ids, token_scores, arrive, stream);
 }
 
 }  // namespace
@@ -159,6 +160,7 @@ Workspace plan_workspace(const Problem& P, int K_b, int K_t, unsigned regions, i
   take(&w.dkeys, kWsDense, U * size_t(P.T) * sizeof(uint32_t));  // token-only operator
   take(&w.dstats, kWsDense, ds_stats_floats(P) * sizeof(float));
   take(&w.dhist, kWsDenseHist, ds_hist_words(P) * sizeof(uint32_t));
+  take(&w.arrive, kWsArrive, U * sizeof(uint32_t));
   w.total = off;
   return w;
 }
@@ -340,7 +342,7 @@ tls_status tls_select_blocks(const tls_layout* layout, const void* q, const void
   if (ws_bytes < W.total) return TLS_ERR_WORKSPACE_TOO_SMALL;
   float* scores = block_scores ? block_scores : at<float>(ws, W.bscores);
   hipError_t e = tls::launch_block_score(P, q, kmax, kmin, ctx_lens, at<float>(ws, W.qpn), scores, err_word(ws), stream);
-  if (e == hipSuccess) e = tls::launch_block_topk(P, scores, ctx_lens, K_b, block_ids, err_word(ws), stream);
+  if (e == hipSuccess) e = tls::launch_block_topk(P, scores, ctx_lens, K_b, block_ids, nullptr, stream);
   return hip_status(e);
 }
 
@@ -359,10 +361,10 @@ tls_status tls_select_tokens(const tls_layout* layout, const void* q, const uint
   if (ws_bytes < W.total) return TLS_ERR_WORKSPACE_TOO_SMALL;
   if (tls::fused_token_select_ok(P, K_b, K_t))
     return hip_status(tls::launch_token_select_fused(P, q, codes, qparams, channels, nullptr, block_ids, nullptr,
-                                                     ctx_lens, K_b, K_t, token_ids, token_scores, err_word(ws),
-                                                     stream));
+                                                     ctx_lens, K_b, K_t, token_ids, token_scores, nullptr,
+                                                     err_word(ws), stream));
   return hip_status(run_token_select(P, W, q, codes, qparams, channels, block_ids, K_b, ctx_lens, K_t, token_ids,
-                                     token_scores, ws, err_word(ws), stream, nullptr));
+                                     token_scores, ws, nullptr, err_word(ws), stream, nullptr));
 }
 
 }  // extern "C"
@@ -408,11 +410,18 @@ struct WsTarget {
   bool compact;
   // Plans the workspace for a route using `regions` (split partials for
   // `nsplit` splits) and binds its memory: TLS_ERR_WORKSPACE_TOO_SMALL when
-  // the plan does not fit.  The library scratch is looked up only here, after
-  // every argument check, so a rejected call touches no device.
-  tls_status bind(const Problem& P, int K_b, int K_t, unsigned regions, int nsplit, tls::Workspace* W, void** ws,
-                  uint32_t** err_word_out) const {
-    *W = compact ? tls::plan_workspace(P, K_b, K_t, regions, nsplit) : tls::plan_workspace(P, K_b, K_t);
+  // the plan does not fit.  `optional` holds the regions of `*regions` that
+  // the route can do without: they are dropped from it where the library
+  // scratch would be too small with them.  The library scratch is looked up
+  // only here, after every argument check, so a rejected call touches no
+  // device.
+  tls_status bind(const Problem& P, int K_b, int K_t, unsigned* regions, unsigned optional, int nsplit,
+                  tls::Workspace* W, void** ws, uint32_t** err_word_out) const {
+    *W = compact ? tls::plan_workspace(P, K_b, K_t, *regions, nsplit) : tls::plan_workspace(P, K_b, K_t);
+    if (bytes < W->total && compact && (*regions & optional)) {
+      *regions &= ~optional;
+      *W = tls::plan_workspace(P, K_b, K_t, *regions, nsplit);
+    }
     if (bytes < W->total) return TLS_ERR_WORKSPACE_TOO_SMALL;
     if (base) {
       *ws = base;
@@ -430,14 +439,16 @@ struct WsTarget {
 // whether it writes partials (everything but the whole-unit kernel does).
 int attention_route(const Problem& P, int n_list, int requested, unsigned* regions) {
   const int nsplit = tls::attn_splits_for(P, n_list, requested);
-  if (!(nsplit == 1 && tls::gqa_whole_ok(P, n_list))) *regions |= tls::kWsSplit;
+  if (!(nsplit == 1 && tls::gqa_whole_ok(P, n_list))) *regions |= tls::kWsSplit | tls::kWsArrive;
   return nsplit;
 }
 
 // Attention over a work list (stages 6 and 7): n_list entries per unit.
+// arrive: the units' split arrivals, cleared by an earlier kernel of the call,
+// or NULL.
 tls_status finish_decode(const Problem& P, const tls::Workspace& W, const void* q, const tls_kv_view* kv,
                          const int32_t* ctx_lens, int n_list, int nsplit, const tls::TokenList& tl, void* out,
-                         float* lse, void* ws, uint32_t* err, hipEvent_t* ev, hipStream_t stream) {
+                         float* lse, void* ws, uint32_t* arrive, uint32_t* err, hipEvent_t* ev, hipStream_t stream) {
   tls::KvView view{kv->k, kv->v, kv->slot_map, kv->n_slots};
   if (nsplit == 1 && tls::gqa_whole_ok(P, n_list)) {
     const hipError_t e = tls::launch_attention_gqa_whole(P, q, view, tl, ctx_lens, n_list, out, lse, err, stream);
@@ -445,10 +456,11 @@ tls_status finish_decode(const Problem& P, const tls::Workspace& W, const void* 
     if (ev) (void)hipEventRecord(ev[7], stream);
     return hip_status(e);
   }
-  hipError_t e = tls::launch_attention(P, q, view, tl, ctx_lens, n_list, nsplit, at<float>(ws, W.po),
-                                       at<float>(ws, W.plse), err, stream);
+  const tls::SplitOut so{at<float>(ws, W.po), at<float>(ws, W.plse), arrive, out, lse};
+  bool merged = false;
+  hipError_t e = tls::launch_attention(P, q, view, tl, ctx_lens, n_list, nsplit, so, err, stream, &merged);
   if (ev) (void)hipEventRecord(ev[6], stream);
-  if (e == hipSuccess) e = tls::launch_merge(P, at<float>(ws, W.po), at<float>(ws, W.plse), nsplit, out, lse, stream);
+  if (e == hipSuccess && !merged) e = tls::launch_merge(P, at<float>(ws, W.po), at<float>(ws, W.plse), nsplit, out, lse, stream);
   if (ev) (void)hipEventRecord(ev[7], stream);
   return hip_status(e);
 }
@@ -471,14 +483,10 @@ tls_status token_level_decode(const Problem& P, const void* q, const tls_kv_view
   tls::Workspace W;
   void* ws = nullptr;
   uint32_t* err = nullptr;
-  // with the bucket counts where they fit the library's scratch too
-  bool counts = true;
-  st = tgt.bind(P, K_b > 0 ? K_b : 1, K_t, regions | tls::kWsDenseHist, nsplit, &W, &ws, &err);
-  if (st == TLS_ERR_WORKSPACE_TOO_SMALL && tgt.compact) {
-    counts = false;
-    st = tgt.bind(P, K_b > 0 ? K_b : 1, K_t, regions, nsplit, &W, &ws, &err);
-  }
+  regions |= tls::kWsDenseHist;
+  st = tgt.bind(P, K_b > 0 ? K_b : 1, K_t, &regions, tls::kWsDenseHist | tls::kWsArrive, nsplit, &W, &ws, &err);
   if (st != TLS_OK) return st;
+  uint32_t* arrive = regions & tls::kWsArrive ? at<uint32_t>(ws, W.arrive) : nullptr;
   auto mark = [&](int i) {
     if (ev) (void)hipEventRecord(ev[i], stream);
   };
@@ -488,13 +496,14 @@ tls_status token_level_decode(const Problem& P, const void* q, const tls_kv_view
   int32_t* to = token_ids_out ? token_ids_out : at<int32_t>(ws, W.tids);
   const hipError_t e = tls::launch_token_select_dense(P, q, codes, qparams, channels, ctx_lens, K_t,
                                                       at<float>(ws, W.dstats), at<uint32_t>(ws, W.dkeys),
-                                                      counts ? at<uint32_t>(ws, W.dhist) : nullptr, to, err, stream);
+                                                      regions & tls::kWsDenseHist ? at<uint32_t>(ws, W.dhist) : nullptr,
+                                                      to, arrive, err, stream);
   mark(3);
   mark(4);
   mark(5);
   if (e != hipSuccess) return TLS_ERR_HIP;
   return finish_decode(P, W, q, kv, ctx_lens, K_t, nsplit, tls::TokenList{to, K_t, tls::kListIds, P.B}, out, lse,
-                       ws, err, ev, stream);
+                       ws, arrive, err, ev, stream);
 }
 
 // The single-level baselines (TLS_MODE_BLOCK_SPARSE, TLS_MODE_DENSE): block
@@ -524,8 +533,10 @@ tls_status single_level_decode(const Problem& P, int mode, const void* q, const 
   tls::Workspace W;
   void* ws = nullptr;
   uint32_t* err = nullptr;
-  st = tgt.bind(P, dense ? 1 : K_b, K_t > 0 ? K_t : 1, regions, nsplit, &W, &ws, &err);
+  if (!sel) regions &= ~tls::kWsArrive;  // no kernel before the attention clears the arrivals
+  st = tgt.bind(P, dense ? 1 : K_b, K_t > 0 ? K_t : 1, &regions, tls::kWsArrive, nsplit, &W, &ws, &err);
   if (st != TLS_OK) return st;
+  uint32_t* arrive = regions & tls::kWsArrive ? at<uint32_t>(ws, W.arrive) : nullptr;
   auto mark = [&](int i) {
     if (ev) (void)hipEventRecord(ev[i], stream);
   };
@@ -537,7 +548,7 @@ tls_status single_level_decode(const Problem& P, int mode, const void* q, const 
     e = tls::launch_block_score(P, q, kmax, kmin, ctx_lens, at<float>(ws, W.qpn), at<float>(ws, W.bscores), err,
                                 stream);
     mark(1);
-    if (e == hipSuccess) e = tls::launch_block_topk(P, at<float>(ws, W.bscores), ctx_lens, K_b, bo, err, stream);
+    if (e == hipSuccess) e = tls::launch_block_topk(P, at<float>(ws, W.bscores), ctx_lens, K_b, bo, arrive, stream);
     bids = bo;
   } else {
     mark(1);
@@ -546,7 +557,7 @@ tls_status single_level_decode(const Problem& P, int mode, const void* q, const 
   if (e != hipSuccess) return TLS_ERR_HIP;
   const tls::TokenList tl = dense ? tls::TokenList{nullptr, 0, tls::kListAll, P.B}
                                   : tls::TokenList{bids, K_b, tls::kListBlocks, P.B};
-  return finish_decode(P, W, q, kv, ctx_lens, n_list, nsplit, tl, out, lse, ws, err, ev, stream);
+  return finish_decode(P, W, q, kv, ctx_lens, n_list, nsplit, tl, out, lse, ws, arrive, err, ev, stream);
 }
 
 // tls_sparse_decode after the layout is validated, on a workspace target.
@@ -605,8 +616,10 @@ tls_status sparse_decode_on(const Problem& P, const void* q, const tls_kv_view* 
   tls::Workspace W;
   void* ws = nullptr;
   uint32_t* err = nullptr;
-  st = tgt.bind(P, K_b, K_t, regions, nsplit, &W, &ws, &err);
+  if (!sel_tokens) regions &= ~tls::kWsArrive;  // no kernel before the attention clears the arrivals
+  st = tgt.bind(P, K_b, K_t, &regions, tls::kWsArrive, nsplit, &W, &ws, &err);
   if (st != TLS_OK) return st;
+  uint32_t* arrive = regions & tls::kWsArrive ? at<uint32_t>(ws, W.arrive) : nullptr;
 
   hipError_t e = hipSuccess;
   auto mark = [&](int i) {
@@ -627,21 +640,21 @@ tls_status sparse_decode_on(const Problem& P, const void* q, const tls_kv_view* 
     mark(2);
     if (e == hipSuccess)
       e = tls::launch_token_select_fused(P, q, codes, qparams, channels, bsc, block_ids_in,
-                                         sel_blocks ? block_ids_out : nullptr, ctx_lens, K_b, K_t, to, nullptr, err,
-                                         stream);  // scores and a given list: the lagged operator
+                                         sel_blocks ? block_ids_out : nullptr, ctx_lens, K_b, K_t, to, nullptr, arrive,
+                                         err, stream);  // scores and a given list: the lagged operator
     mark(3);
     mark(4);
     mark(5);
     if (e != hipSuccess) return TLS_ERR_HIP;
     return finish_decode(P, W, q, kv, ctx_lens, K_t, nsplit, tls::TokenList{to, K_t, tls::kListIds, P.B}, out, lse,
-                         ws, err, ev, stream);
+                         ws, arrive, err, ev, stream);
   }
   if (sel_blocks) {
     int32_t* bo = block_ids_out ? block_ids_out : at<int32_t>(ws, W.bids);
     e = tls::launch_block_score(P, q, kmax, kmin, ctx_lens, at<float>(ws, W.qpn), at<float>(ws, W.bscores), err,
                                 stream);
     mark(1);
-    if (e == hipSuccess) e = tls::launch_block_topk(P, at<float>(ws, W.bscores), ctx_lens, K_b, bo, err, stream);
+    if (e == hipSuccess) e = tls::launch_block_topk(P, at<float>(ws, W.bscores), ctx_lens, K_b, bo, nullptr, stream);
     if (!lagged) bids = bo;  // the lagged operator selects tokens from the given blocks
   } else {
     mark(1);
@@ -651,8 +664,8 @@ tls_status sparse_decode_on(const Problem& P, const void* q, const tls_kv_view* 
   const int32_t* tids = token_ids_in;
   if (sel_tokens) {
     int32_t* to = token_ids_out ? token_ids_out : at<int32_t>(ws, W.tids);
-    e = run_token_select(P, W, q, codes, qparams, channels, bids, K_b, ctx_lens, K_t, to, nullptr, ws, err, stream,
-                         ev ? ev + 3 : nullptr);
+    e = run_token_select(P, W, q, codes, qparams, channels, bids, K_b, ctx_lens, K_t, to, nullptr, ws, arrive, err,
+                         stream, ev ? ev + 3 : nullptr);
     tids = to;
   } else {
     mark(3);
@@ -661,7 +674,7 @@ tls_status sparse_decode_on(const Problem& P, const void* q, const tls_kv_view* 
   mark(5);
   if (e != hipSuccess) return TLS_ERR_HIP;
   return finish_decode(P, W, q, kv, ctx_lens, K_t, nsplit, tls::TokenList{tids, K_t, tls::kListIds, P.B}, out, lse,
-                       ws, err, ev, stream);
+                       ws, arrive, err, ev, stream);
 }
 
 }  // namespace

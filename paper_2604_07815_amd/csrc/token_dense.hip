@@ -741,12 +741,14 @@ __device__ inline void ds_select_list(const uint32_t* keys, const int32_t* list,
 __global__ __launch_bounds__(kDsTopkThreads) void ds_topk_kernel(const uint32_t* __restrict__ keys,
                                                                   const uint32_t* __restrict__ hist,
                                                                   const int32_t* __restrict__ ctx_lens, int H_kv,
-                                                                  int T, int K_t, int32_t* __restrict__ token_ids) {
+                                                                  int T, int K_t, int32_t* __restrict__ token_ids,
+                                                                  uint32_t* arrive) {
   constexpr int NT = kDsTopkThreads, EPT = kTopkMaxEPT, TILE = NT * EPT;
   extern __shared__ uint32_t smem[];
   uint32_t* scratch = smem;
   uint32_t* list = smem + topk_scratch_words(NT);
   const int unit = blockIdx.x, tid = threadIdx.x;
+  if (arrive && tid == 0) arrive[unit] = 0u;
   int n = ctx_lens[unit / H_kv];
   n = n < 0 ? 0 : (n > T ? T : n);
   const uint32_t* uk = keys + size_t(unit) * T;
@@ -874,8 +876,8 @@ static void launch_ds_wide(const Problem& P, const DsArgs& a, dim3 grid, int nch
 
 hipError_t launch_token_select_dense(const Problem& P, const void* q, const uint8_t* codes, const float* qparams,
                                      const int32_t* channels, const int32_t* ctx_lens, int K_t, float* stats,
-                                     uint32_t* keys, uint32_t* hist, int32_t* token_ids, uint32_t* err,
-                                     hipStream_t st) {
+                                     uint32_t* keys, uint32_t* hist, int32_t* token_ids, uint32_t* arrive,
+                                     uint32_t* err, hipStream_t st) {
   if (!ds_supported(P)) return hipErrorInvalidValue;
   const DsArgs a{q, codes, qparams, channels, ctx_lens, stats, keys, hist, err};
   const int ch = ds_chunk_tokens(P), nchunks = (P.T + ch - 1) / ch;
@@ -910,7 +912,7 @@ hipError_t launch_token_select_dense(const Problem& P, const void* q, const uint
   const size_t lds = (size_t(topk_scratch_words(kDsTopkThreads)) + kDsListCap) * sizeof(uint32_t);
   e = allow_dynamic_lds(reinterpret_cast<const void*>(ds_topk_kernel), lds);
   if (e != hipSuccess) return e;
-  ds_topk_kernel<<<P.units, kDsTopkThreads, lds, st>>>(keys, hist, ctx_lens, P.H_kv, P.T, K_t, token_ids);
+  ds_topk_kernel<<<P.units, kDsTopkThreads, lds, st>>>(keys, hist, ctx_lens, P.H_kv, P.T, K_t, token_ids, arrive);
   return hipGetLastError();
 }
 

@@ -693,12 +693,13 @@ __global__ __launch_bounds__(1024) void token_topk_kernel(const uint32_t* __rest
                                                            const uint32_t* __restrict__ kinfo,
                                                            const int32_t* __restrict__ block_ids, int K_b,
                                                            int B, int K_t, int32_t* __restrict__ token_ids,
-                                                           float* __restrict__ token_scores) {
+                                                           float* __restrict__ token_scores, uint32_t* arrive) {
   extern __shared__ uint32_t smem[];
   uint32_t* scratch = smem;
   int32_t* s_bl = reinterpret_cast<int32_t*>(smem + topk_scratch_words(1024));
   const int S = K_b * B;
   const int unit = blockIdx.x;
+  if (arrive && threadIdx.x == 0) arrive[unit] = 0u;
   uint32_t kr[EPT];
 #pragma unroll
   for (int j = 0; j < EPT; ++j) {
@@ -795,14 +796,15 @@ hipError_t launch_token_alpha(const Problem& P, const float* logits, const float
 }
 
 hipError_t launch_token_topk(const Problem& P, const uint32_t* keys, const uint32_t* kinfo, const int32_t* block_ids,
-                             int K_b, int K_t, int32_t* token_ids, float* token_scores, hipStream_t st) {
+                             int K_b, int K_t, int32_t* token_ids, float* token_scores, uint32_t* arrive,
+                             hipStream_t st) {
   const int S = K_b * P.B;
   const size_t lds = (topk_scratch_words(1024) + size_t(align4w(K_b))) * sizeof(uint32_t);
   const int ept = (S + 1023) / 1024;
   auto go = [&](auto kern) {
     const hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(kern), lds);
     if (e != hipSuccess) return e;
-    kern<<<P.units, 1024, lds, st>>>(keys, kinfo, block_ids, K_b, P.B, K_t, token_ids, token_scores);
+    kern<<<P.units, 1024, lds, st>>>(keys, kinfo, block_ids, K_b, P.B, K_t, token_ids, token_scores, arrive);
     return hipGetLastError();
   };
   if (ept <= 1) return go(token_topk_kernel<1>);

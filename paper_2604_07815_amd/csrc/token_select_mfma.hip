@@ -36,8 +36,9 @@ __global__ __launch_bounds__(kSelNT) void token_select_mfma_kernel(
     const int32_t* __restrict__ channels, const float* __restrict__ block_scores,
     const int32_t* __restrict__ block_ids_in, int32_t* __restrict__ block_ids_out,
     const int32_t* __restrict__ ctx_lens, int H_q, int H_kv, int d, int B, int T, int m_max, int K_b, int K_t,
-    float sigma, int32_t* __restrict__ token_ids, float* __restrict__ token_scores, uint32_t* err) {
+    float sigma, int32_t* __restrict__ token_ids, float* __restrict__ token_scores, uint32_t* arrive, uint32_t* err) {
   extern __shared__ uint32_t smem[];
+  if (arrive && threadIdx.x == 0) arrive[blockIdx.x] = 0u;
   token_select_mfma_body<G, WB>(smem, q, codes, qparams, channels, block_scores, block_ids_in, block_ids_out, ctx_lens,
                             H_q, H_kv, d, B, T, m_max, K_b, K_t, sigma, token_ids, token_scores, err, blockIdx.x);
 }
@@ -52,14 +53,15 @@ template <int G, bool WB>
 static hipError_t launch_gw(const Problem& P, const void* q, const uint8_t* codes, const float* qparams,
                            const int32_t* channels, const float* block_scores, const int32_t* block_ids_in,
                            int32_t* block_ids_out, const int32_t* ctx_lens, int K_b, int K_t, int32_t* token_ids,
-                           float* token_scores, uint32_t* err, hipStream_t st) {
+                           float* token_scores, uint32_t* arrive, uint32_t* err,
+                           hipStream_t st) {
   const size_t lds = mfma_select_lds_bytes(K_b);
   auto kern = token_select_mfma_kernel<G, WB>;
   const hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(kern), lds);
   if (e != hipSuccess) return e;
   kern<<<P.units, kSelNT, lds, st>>>((const uint16_t*)q, codes, qparams, channels, block_scores, block_ids_in,
                                      block_ids_out, ctx_lens, P.H_q, P.H_kv, P.d_qk, P.B, P.T, P.m_max, K_b, K_t,
-                                     P.sigma, token_ids, token_scores, err);
+                                     P.sigma, token_ids, token_scores, arrive, err);
   return hipGetLastError();
 }
 
@@ -67,28 +69,29 @@ template <int G>
 static hipError_t launch_g(const Problem& P, const void* q, const uint8_t* codes, const float* qparams,
                            const int32_t* channels, const float* block_scores, const int32_t* block_ids_in,
                            int32_t* block_ids_out, const int32_t* ctx_lens, int K_b, int K_t, int32_t* token_ids,
-                           float* token_scores, uint32_t* err, hipStream_t st) {
+                           float* token_scores, uint32_t* arrive, uint32_t* err,
+                           hipStream_t st) {
   if (P.B >= 64)
     return launch_gw<G, true>(P, q, codes, qparams, channels, block_scores, block_ids_in, block_ids_out, ctx_lens,
-                              K_b, K_t, token_ids, token_scores, err, st);
+                              K_b, K_t, token_ids, token_scores, arrive, err, st);
   return launch_gw<G, false>(P, q, codes, qparams, channels, block_scores, block_ids_in, block_ids_out, ctx_lens,
-                             K_b, K_t, token_ids, token_scores, err, st);
+                             K_b, K_t, token_ids, token_scores, arrive, err, st);
 }
 
 hipError_t launch_token_select_fused(const Problem& P, const void* q, const uint8_t* codes, const float* qparams,
                                      const int32_t* channels, const float* block_scores,
                                      const int32_t* block_ids_in, int32_t* block_ids_out, const int32_t* ctx_lens,
-                                     int K_b, int K_t, int32_t* token_ids, float* token_scores, uint32_t* err,
-                                     hipStream_t st) {
+                                     int K_b, int K_t, int32_t* token_ids, float* token_scores, uint32_t* arrive,
+                                     uint32_t* err, hipStream_t st) {
   switch (P.G) {
     case 1: return launch_g<1>(P, q, codes, qparams, channels, block_scores, block_ids_in, block_ids_out, ctx_lens,
-                               K_b, K_t, token_ids, token_scores, err, st);
+                               K_b, K_t, token_ids, token_scores, arrive, err, st);
     case 2: return launch_g<2>(P, q, codes, qparams, channels, block_scores, block_ids_in, block_ids_out, ctx_lens,
-                               K_b, K_t, token_ids, token_scores, err, st);
+                               K_b, K_t, token_ids, token_scores, arrive, err, st);
     case 3: return launch_g<3>(P, q, codes, qparams, channels, block_scores, block_ids_in, block_ids_out, ctx_lens,
-                               K_b, K_t, token_ids, token_scores, err, st);
+                               K_b, K_t, token_ids, token_scores, arrive, err, st);
     default: return launch_g<4>(P, q, codes, qparams, channels, block_scores, block_ids_in, block_ids_out, ctx_lens,
-                                K_b, K_t, token_ids, token_scores, err, st);
+                                K_b, K_t, token_ids, token_scores, arrive, err, st);
   }
 }
 
