@@ -74,12 +74,13 @@ hipError_t launch_block_topk(const Problem& P, const float* scores, const int32_
 hipError_t launch_token_score(const Problem& P, const void* q, const uint8_t* codes, const float* qparams,
                               const int32_t* channels, const int32_t* block_ids, int K_b,
                               const int32_t* ctx_lens, float* logits, float* stats, int n_tchunks,
-                              uint32_t* err, hipStream_t st);
-hipError_t launch_token_alpha(const Problem& P, const float* logits, const float* stats, int n_tchunks,
-                              const int32_t* block_ids, int K_b, const int32_t* ctx_lens, uint32_t* keys, uint32_t* kinfo,
-                              hipStream_t st);
-hipError_t launch_token_topk(const Problem& P, const uint32_t* keys, const uint32_t* kinfo, const int32_t* block_ids, int K_b,
-                             int K_t, int32_t* token_ids, float* token_scores, uint32_t* arrive, hipStream_t st);
+                              uint32_t* kinfo, uint32_t* err, hipStream_t st);
+// alpha keys and the top-K_t.  kinfo: two words per unit, the first cleared by
+// launch_token_score.
+hipError_t launch_token_alpha_topk(const Problem& P, const float* logits, const float* stats, int n_tchunks,
+                                   const int32_t* block_ids, int K_b, const int32_t* ctx_lens, int K_t, uint32_t* keys,
+                                   uint32_t* kinfo, int32_t* token_ids, float* token_scores, uint32_t* arrive,
+                                   hipStream_t st);
 
 // One work-group per unit: (optional) block top-k from block_scores, then the
 // whole token selection on chip, over the selected blocks or, when

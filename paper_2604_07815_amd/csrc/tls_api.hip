@@ -118,15 +118,15 @@ hipError_t run_token_select(const Problem& P, const tls::Workspace& W, const voi
                             const int32_t* ctx_lens, int K_t, int32_t* token_ids, float* token_scores, void* ws,
                             uint32_t* arrive, uint32_t* err, hipStream_t stream, hipEvent_t* ev) {
   hipError_t e = tls::launch_token_score(P, q, codes, qparams, channels, block_ids, K_b, ctx_lens,
-                                         at<float>(ws, W.logits), at<float>(ws, W.stats), W.n_tchunks, err, stream);
+                                         at<float>(ws, W.logits), at<float>(ws, W.stats), W.n_tchunks,
+                                         at<uint32_t>(ws, W.kinfo), err, stream);
   if (e != hipSuccess) return e;
   if (ev) (void)hipEventRecord(ev[0], stream);
-  e = tls::launch_token_alpha(P, at<float>(ws, W.logits), at<float>(ws, W.stats), W.n_tchunks, block_ids, K_b,
-                              ctx_lens, at<uint32_t>(ws, W.keys), at<uint32_t>(ws, W.kinfo), stream);
-  if (e != hipSuccess) return e;
+  // the normalisation and the top-k are one launch for most head counts
   if (ev) (void)hipEventRecord(ev[1], stream);
-  return tls::launch_token_topk(P, at<uint32_t>(ws, W.keys), at<uint32_t>(ws, W.kinfo), block_ids, K_b, K_t,
-                                token_ids, token_scores, arrive, stream);
+  return tls::launch_token_alpha_topk(P, at<float>(ws, W.logits), at<float>(ws, W.stats), W.n_tchunks, block_ids, K_b,
+                                      ctx_lens, K_t, at<uint32_t>(ws, W.keys), at<uint32_t>(ws, W.kinfo), token_ids,
+                                      token_scores, arrive, stream);
 }
 
 }  // namespace

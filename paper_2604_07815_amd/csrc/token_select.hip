@@ -14,6 +14,8 @@
 // token_alpha_kernel: per-head normalisers over all candidates, then
 //   alpha_j = (1/G) sum_h exp(l_hj - m_h) / Z_h as an orderable key.
 // token_topk_kernel: the K_t largest alpha, ascending token positions.
+#include <type_traits>
+
 #include "token_common.hpp"
 
 namespace tls {
@@ -26,12 +28,13 @@ __global__ __launch_bounds__(256) void token_score_kernel(
     const typename E::T* __restrict__ q, const uint8_t* __restrict__ codes, const float* __restrict__ qparams,
     const int32_t* __restrict__ channels, const int32_t* __restrict__ block_ids, int K_b,
     const int32_t* __restrict__ ctx_lens, int H_q, int H_kv, int G, int d, int d_c, int B, int T, float sigma,
-    float* __restrict__ logits, float* __restrict__ stats, uint32_t* err) {
+    float* __restrict__ logits, float* __restrict__ stats, uint32_t* __restrict__ kinfo, uint32_t* err) {
   __shared__ float s_qt[kMaxG * 256];
   __shared__ float s_qsum[kMaxG * kMaxGroups];
   __shared__ float s_red[4 * kMaxG];
   __shared__ int s_ch[kMaxGroups * 32];
   const int unit = blockIdx.y, chunk = blockIdx.x;
+  if (chunk == 0 && threadIdx.x == 0) kinfo[2 * size_t(unit)] = 0u;  // arrivals of the alpha stage
   const int s = unit / H_kv, g = unit % H_kv;
   int n = ctx_lens[s];
   n = n < 0 ? 0 : (n > T ? T : n);
@@ -164,10 +167,11 @@ __global__ __launch_bounds__(256) void token_score_row_kernel(
     const typename E::T* __restrict__ q, const uint8_t* __restrict__ codes, const float* __restrict__ qparams,
     const int32_t* __restrict__ channels, const int32_t* __restrict__ block_ids, int K_b,
     const int32_t* __restrict__ ctx_lens, int H_q, int H_kv, int d, int d_c, int B, int T, float sigma,
-    float* __restrict__ logits, float* __restrict__ stats, uint32_t* err) {
+    float* __restrict__ logits, float* __restrict__ stats, uint32_t* __restrict__ kinfo, uint32_t* err) {
   __shared__ __attribute__((aligned(16))) float s_q[kMaxGroups * 32 * G];  // [channel][head]
   __shared__ float s_red[4][G][2];
   const int unit = blockIdx.y, chunk = blockIdx.x;
+  if (chunk == 0 && threadIdx.x == 0) kinfo[2 * size_t(unit)] = 0u;  // arrivals of the alpha stage
   const int s = unit / H_kv, g = unit % H_kv;
   const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
   const int S = K_b * B, ngr = d_c / 32;
@@ -250,11 +254,12 @@ __global__ __launch_bounds__(256) void token_score_lane_kernel(
     const uint16_t* __restrict__ q, const uint8_t* __restrict__ codes, const float* __restrict__ qparams,
     const int32_t* __restrict__ channels, const int32_t* __restrict__ block_ids, int K_b,
     const int32_t* __restrict__ ctx_lens, int H_q, int H_kv, int G, int d, int B, int T, float sigma,
-    float* __restrict__ logits, float* __restrict__ stats, uint32_t* err) {
+    float* __restrict__ logits, float* __restrict__ stats, uint32_t* __restrict__ kinfo, uint32_t* err) {
   constexpr int DC = 32 * NGR, NQ = NGR * HS * 128, PER = (NQ + 255) / 256;
   __shared__ __attribute__((aligned(16))) uint16_t s_qt[NQ];  // [group][set][head][position]
   __shared__ float s_red[4][4 * HS][2];
   const int unit = blockIdx.y, chunk = blockIdx.x;
+  if (chunk == 0 && threadIdx.x == 0) kinfo[2 * size_t(unit)] = 0u;  // arrivals of the alpha stage
   const int s = unit / H_kv, g = unit % H_kv;
   const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
   const int S = K_b * B;
@@ -352,7 +357,7 @@ __global__ __launch_bounds__(256) void token_score_mfma_kernel(
     const uint16_t* __restrict__ q, const uint8_t* __restrict__ codes, const float* __restrict__ qparams,
     const int32_t* __restrict__ channels, const int32_t* __restrict__ block_ids, int K_b,
     const int32_t* __restrict__ ctx_lens, int H_q, int H_kv, int d, int B, int T, float sigma,
-    float* __restrict__ logits, float* __restrict__ stats, uint32_t* err) {
+    float* __restrict__ logits, float* __restrict__ stats, uint32_t* __restrict__ kinfo, uint32_t* err) {
   constexpr int G = 16 * HT, DC = 32 * NGR;
   constexpr uint32_t kBase = 0x43434343u;  // high byte of bf16(128 + c), c < 16
   // q~ in operand order: [head][group][lane group g][8], channel g*8 + {0,2,4,6,1,3,5,7}
@@ -360,6 +365,7 @@ __global__ __launch_bounds__(256) void token_score_mfma_kernel(
   __shared__ float s_qs[G * NGR];
   __shared__ float s_red[4][G][2];
   const int unit = blockIdx.y, chunk = blockIdx.x;
+  if (chunk == 0 && threadIdx.x == 0) kinfo[2 * size_t(unit)] = 0u;  // arrivals of the alpha stage
   const int s = unit / H_kv, g = unit % H_kv;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int t16 = lane & 15, lg = lane >> 4;
@@ -604,32 +610,46 @@ __global__ __launch_bounds__(256) void token_alpha_kernel(
   }
 }
 
-// token_alpha_kernel with the head count fixed at compile time, for a grid
-// of one slot per thread: 256/G lanes combine each head's work-group
-// statistics, and every request of a work-group leaves at once before the
-// first is used (its lanes' statistics, the block-list entries of its slots
-// and of the unit information, the slots' G logits; unconditional loads at
-// clamped addresses), so the kernel waits for one memory round trip.
-template <int G>
-__global__ __launch_bounds__(256) void token_alpha_kernel_g(
+// Alpha and the top-K_t in one launch, for G = 4, 8, 16, 32: a work-group of
+// 1024 threads computes the keys of 1024 slots, stores them past the L2s (as
+// SplitOut's partials) and counts itself in; the unit's last one reads all of
+// them back into registers and selects, from bounds it knows (each exponential
+// is <= 1, so alpha is at most (1/G) sum_h 1/Z_h summed in the key loop's
+// order).  A latency chain: every request of a work-group leaves at once
+// before the first is used (statistics, block-list entries, the slot's G
+// logits; unconditional loads at clamped addresses).  With one work-group per
+// unit it is a single pass.  Against an alpha and a top-K_t launch: 2 units of
+// 512 slots 6.6 -> 4.8 us, 32 units of 8 heads and 4096 slots 9.9 -> 9.4, MLA
+// (8 units of 32 heads, 8192 slots) 13.4 either way: storing, counting and
+// reading back cost what a launch does, and spreading a slot's heads over four
+// threads changed nothing (14.0).
+template <int G, int EPT>
+__global__ __launch_bounds__(1024) void token_alpha_topk_kernel(
     const float* __restrict__ logits, const float* __restrict__ stats, int n_tchunks,
     const int32_t* __restrict__ block_ids, int K_b, const int32_t* __restrict__ ctx_lens, int H_kv, int B, int T,
-    uint32_t* __restrict__ keys, uint32_t* __restrict__ kinfo) {
-  constexpr int TPH = 256 / G;  // lanes per head (a power of two)
-  constexpr int kC = 8;         // statistics chunks per lane requested together
+    int K_t, uint32_t* __restrict__ keys, uint32_t* __restrict__ kinfo, int32_t* __restrict__ token_ids,
+    float* __restrict__ token_scores, uint32_t* arrive) {
+  constexpr int NT = 1024, TPH = 256 / G;  // statistics: TPH lanes per head (a power of two) of the first 256 threads
+  constexpr int kC = 8;                    // statistics chunks per lane requested together
   __shared__ float s_m[G], s_iz[G];
-  __shared__ uint32_t s_cnt[4];
+  __shared__ uint32_t s_cnt[4], s_last;
+  extern __shared__ uint32_t smem[];
+  uint32_t* scratch = smem;
+  int32_t* s_bl = reinterpret_cast<int32_t*>(smem + topk_scratch_words(NT));
   const int unit = blockIdx.y, tid = threadIdx.x;
+  if (arrive && blockIdx.x == 0 && tid == 0) arrive[unit] = 0u;
   const int s = unit / H_kv;
   const int S = K_b * B;
-  const int h = tid / TPH, j = tid % TPH;
+  const int h = (tid & 255) / TPH, j = tid % TPH;
   const float2* st = reinterpret_cast<const float2*>(stats) + size_t(unit) * n_tchunks * G;
   const int32_t* bl = block_ids + size_t(unit) * K_b;
   const float* lg = logits + size_t(unit) * G * S;
-  const int slot = blockIdx.x * 256 + tid, sl = min(slot, S - 1);
+  const int slot = blockIdx.x * NT + tid, sl = min(slot, S - 1);
   float2 sv[kC];
+  if (tid < 256) {
 #pragma unroll
-  for (int c = 0; c < kC; ++c) sv[c] = st[size_t(min(j + c * TPH, n_tchunks - 1)) * G + h];
+    for (int c = 0; c < kC; ++c) sv[c] = st[size_t(min(j + c * TPH, n_tchunks - 1)) * G + h];
+  }
   __builtin_amdgcn_sched_barrier(0);
   const int b_slot = bl[tok_block(sl, B)];
   const int b_first = bl[min(tid, K_b - 1)];
@@ -640,7 +660,9 @@ __global__ __launch_bounds__(256) void token_alpha_kernel_g(
   int n = ctx_lens[s];
   n = n < 0 ? 0 : (n > T ? T : n);
   const int m = (n + B - 1) / B;
-  {
+  topk_prepare<NT>(scratch);
+  for (int i = tid; i < K_b; i += NT) s_bl[i] = i == tid ? b_first : bl[i];
+  if (tid < 256) {
     // chunks j, j + TPH, ... in ascending order, then the lanes' tree (the
     // requested entries are used through selects, not branches, so that
     // no load is sunk into a branch; adding +0 leaves Z >= +0 unchanged)
@@ -668,21 +690,56 @@ __global__ __launch_bounds__(256) void token_alpha_kernel_g(
       s_m[h] = M;
       s_iz[h] = Z > 0.f ? 1.0f / Z : 0.f;
     }
+    // the unit's valid candidates
+    uint32_t c = 0;
+    for (int i = tid; i < K_b; i += 256) {
+      const int b = i == tid ? b_first : bl[i];
+      if (b >= 0 && b < m) c += uint32_t(min(B, n - b * B));
+    }
+    c = wave_reduce_bits(c, [](uint32_t a, uint32_t b) { return a + b; });
+    if ((tid & 63) == 0) s_cnt[tid >> 6] = c;
   }
   __syncthreads();
   const float invG = 1.0f / float(G);
-  if (blockIdx.x == 0) write_unit_info(bl, b_first, K_b, B, m, n, s_iz, G, invG, kinfo, unit, s_cnt);
-  if (slot < S) {
+  uint32_t key = kInvalidKey;
+  {
     const int t = b_slot * B + tok_offset(slot, B);
-    uint32_t key = kInvalidKey;
-    if (b_slot >= 0 && b_slot < m && t < n) {
+    if (slot < S && b_slot >= 0 && b_slot < m && t < n) {
       float a = 0.f;
 #pragma unroll
       for (int hh = 0; hh < G; ++hh) a += __expf(v[hh] - s_m[hh]) * s_iz[hh];
       key = alpha_key(a * invG);
     }
-    keys[size_t(unit) * S + slot] = key;
   }
+  uint32_t kr[EPT];
+  if (EPT == 1 || gridDim.x == 1) {
+    kr[0] = key;
+#pragma unroll
+    for (int e = 1; e < EPT; ++e) kr[e] = kInvalidKey;
+  } else {
+    uint32_t* uk = keys + size_t(unit) * S;
+    if (slot < S) __hip_atomic_store(uk + slot, key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    asm volatile("s_waitcnt vmcnt(0)" : : : "memory");  // this wave's keys are in memory
+    __syncthreads();
+    if (tid == 0) s_last = __hip_atomic_fetch_add(kinfo + 2 * size_t(unit), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    if (s_last != gridDim.x - 1) return;  // uniform
+    asm volatile("" : : : "memory");
+#pragma unroll
+    for (int e = 0; e < EPT; ++e) {
+      const int p = tid + e * NT;
+      kr[e] = __hip_atomic_load(uk + min(p, S - 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (p >= S) kr[e] = kInvalidKey;
+    }
+  }
+  float bsum = 0.f;
+#pragma unroll
+  for (int hh = 0; hh < G; ++hh) bsum = fmaf(1.0f, s_iz[hh], bsum);
+  const TopkKnown known{s_cnt[0] + s_cnt[1] + s_cnt[2] + s_cnt[3], alpha_key(bsum * invG), 0x80000000u};
+  wg_topk_regs<NT, EPT, true>(kr, K_t, token_ids + size_t(unit) * K_t, K_t,
+                              token_scores ? token_scores + size_t(unit) * K_t : nullptr,
+                              [=](int, int p) { return int32_t(s_bl[tok_block(p, B)] * B + tok_offset(p, B)); }, scratch,
+                              &known);
 }
 
 // Top-K_t of the alpha keys of each unit, one work-group per unit.  Thread t
@@ -721,28 +778,29 @@ __global__ __launch_bounds__(1024) void token_topk_kernel(const uint32_t* __rest
 template <int HT, int NGR>
 static void launch_score_mfma(const Problem& P, const void* q, const uint8_t* codes, const float* qparams,
                               const int32_t* channels, const int32_t* block_ids, int K_b, const int32_t* ctx_lens,
-                              float* logits, float* stats, int n_tchunks, uint32_t* err, hipStream_t st) {
+                              float* logits, float* stats, int n_tchunks, uint32_t* kinfo, uint32_t* err,
+                              hipStream_t st) {
   token_score_mfma_kernel<HT, NGR><<<dim3(n_tchunks, P.units), 256, 0, st>>>(
       (const uint16_t*)q, codes, qparams, channels, block_ids, K_b, ctx_lens, P.H_q, P.H_kv, P.d_qk, P.B, P.T,
-      P.sigma, logits, stats, err);
+      P.sigma, logits, stats, kinfo, err);
 }
 
 hipError_t launch_token_score(const Problem& P, const void* q, const uint8_t* codes, const float* qparams,
                               const int32_t* channels, const int32_t* block_ids, int K_b,
-                              const int32_t* ctx_lens, float* logits, float* stats, int n_tchunks,
+                              const int32_t* ctx_lens, float* logits, float* stats, int n_tchunks, uint32_t* kinfo,
                               uint32_t* err, hipStream_t st) {
   if (P.dtype == 1 && (P.G == 16 || P.G == 32) && (P.d_c == 64 || P.d_c == 128)) {
-    if (P.G == 32 && P.d_c == 128) launch_score_mfma<2, 4>(P, q, codes, qparams, channels, block_ids, K_b, ctx_lens, logits, stats, n_tchunks, err, st);
-    else if (P.G == 32) launch_score_mfma<2, 2>(P, q, codes, qparams, channels, block_ids, K_b, ctx_lens, logits, stats, n_tchunks, err, st);
-    else if (P.d_c == 128) launch_score_mfma<1, 4>(P, q, codes, qparams, channels, block_ids, K_b, ctx_lens, logits, stats, n_tchunks, err, st);
-    else launch_score_mfma<1, 2>(P, q, codes, qparams, channels, block_ids, K_b, ctx_lens, logits, stats, n_tchunks, err, st);
+    if (P.G == 32 && P.d_c == 128) launch_score_mfma<2, 4>(P, q, codes, qparams, channels, block_ids, K_b, ctx_lens, logits, stats, n_tchunks, kinfo, err, st);
+    else if (P.G == 32) launch_score_mfma<2, 2>(P, q, codes, qparams, channels, block_ids, K_b, ctx_lens, logits, stats, n_tchunks, kinfo, err, st);
+    else if (P.d_c == 128) launch_score_mfma<1, 4>(P, q, codes, qparams, channels, block_ids, K_b, ctx_lens, logits, stats, n_tchunks, kinfo, err, st);
+    else launch_score_mfma<1, 2>(P, q, codes, qparams, channels, block_ids, K_b, ctx_lens, logits, stats, n_tchunks, kinfo, err, st);
     return hipGetLastError();
   }
   dim3 grid(n_tchunks, P.units);
   if (P.dtype == 1 && P.G <= 8 && (P.d_c == 32 || P.d_c == 64 || P.d_c == 128)) {
     auto go = [&](auto kern) {
       kern<<<grid, 256, 0, st>>>((const uint16_t*)q, codes, qparams, channels, block_ids, K_b, ctx_lens, P.H_q, P.H_kv,
-                                 P.G, P.d_qk, P.B, P.T, P.sigma, logits, stats, err);
+                                 P.G, P.d_qk, P.B, P.T, P.sigma, logits, stats, kinfo, err);
     };
     if (P.G <= 4) {
       if (P.d_c == 32) go(token_score_lane_kernel<1, 1>);
@@ -760,7 +818,7 @@ hipError_t launch_token_score(const Problem& P, const void* q, const uint8_t* co
     using T = typename E::T;
     auto go = [&](auto kern) {
       kern<<<grid, 256, 0, st>>>((const T*)q, codes, qparams, channels, block_ids, K_b, ctx_lens, P.H_q, P.H_kv, P.d_qk,
-                                 P.d_c, P.B, P.T, P.sigma, logits, stats, err);
+                                 P.d_c, P.B, P.T, P.sigma, logits, stats, kinfo, err);
     };
     switch (P.G) {
       case 1: go(token_score_row_kernel<E, 1>); return;
@@ -770,7 +828,7 @@ hipError_t launch_token_score(const Problem& P, const void* q, const uint8_t* co
       default:
         token_score_kernel<E><<<grid, 256, 0, st>>>((const T*)q, codes, qparams, channels, block_ids, K_b, ctx_lens,
                                                     P.H_q, P.H_kv, P.G, P.d_qk, P.d_c, P.B, P.T, P.sigma, logits,
-                                                    stats, err);
+                                                    stats, kinfo, err);
     }
   };
   if (P.dtype == 1) rows(BF16{});
@@ -778,29 +836,40 @@ hipError_t launch_token_score(const Problem& P, const void* q, const uint8_t* co
   return hipGetLastError();
 }
 
-hipError_t launch_token_alpha(const Problem& P, const float* logits, const float* stats, int n_tchunks,
-                              const int32_t* block_ids, int K_b, const int32_t* ctx_lens, uint32_t* keys,
-                              uint32_t* kinfo, hipStream_t st) {
-  const int S = K_b * P.B;
-  dim3 grid((S + 255) / 256, P.units);
-  switch (P.G) {
-    case 4: token_alpha_kernel_g<4><<<grid, 256, 0, st>>>(logits, stats, n_tchunks, block_ids, K_b, ctx_lens, P.H_kv, P.B, P.T, keys, kinfo); break;
-    case 8: token_alpha_kernel_g<8><<<grid, 256, 0, st>>>(logits, stats, n_tchunks, block_ids, K_b, ctx_lens, P.H_kv, P.B, P.T, keys, kinfo); break;
-    case 16: token_alpha_kernel_g<16><<<grid, 256, 0, st>>>(logits, stats, n_tchunks, block_ids, K_b, ctx_lens, P.H_kv, P.B, P.T, keys, kinfo); break;
-    case 32: token_alpha_kernel_g<32><<<grid, 256, 0, st>>>(logits, stats, n_tchunks, block_ids, K_b, ctx_lens, P.H_kv, P.B, P.T, keys, kinfo); break;
-    default:
-      token_alpha_kernel<<<grid, 256, 0, st>>>(logits, stats, n_tchunks, block_ids, K_b, ctx_lens, P.H_kv, P.G,
-                                               P.B, P.T, keys, kinfo);
-  }
-  return hipGetLastError();
-}
-
-hipError_t launch_token_topk(const Problem& P, const uint32_t* keys, const uint32_t* kinfo, const int32_t* block_ids,
-                             int K_b, int K_t, int32_t* token_ids, float* token_scores, uint32_t* arrive,
-                             hipStream_t st) {
+hipError_t launch_token_alpha_topk(const Problem& P, const float* logits, const float* stats, int n_tchunks,
+                                   const int32_t* block_ids, int K_b, const int32_t* ctx_lens, int K_t, uint32_t* keys,
+                                   uint32_t* kinfo, int32_t* token_ids, float* token_scores, uint32_t* arrive,
+                                   hipStream_t st) {
   const int S = K_b * P.B;
   const size_t lds = (topk_scratch_words(1024) + size_t(align4w(K_b))) * sizeof(uint32_t);
   const int ept = (S + 1023) / 1024;
+  auto one = [&](auto kern) {
+    const hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(kern), lds);
+    if (e != hipSuccess) return e;
+    kern<<<dim3(ept, P.units), 1024, lds, st>>>(logits, stats, n_tchunks, block_ids, K_b, ctx_lens, P.H_kv, P.B, P.T,
+                                                K_t, keys, kinfo, token_ids, token_scores, arrive);
+    return hipGetLastError();
+  };
+  auto by_slots = [&](auto g) {
+    constexpr int G = decltype(g)::value;
+    if (ept <= 1) return one(token_alpha_topk_kernel<G, 1>);
+    if (ept <= 2) return one(token_alpha_topk_kernel<G, 2>);
+    if (ept <= 4) return one(token_alpha_topk_kernel<G, 4>);
+    if (ept <= 8) return one(token_alpha_topk_kernel<G, 8>);
+    return one(token_alpha_topk_kernel<G, 16>);
+  };
+  switch (P.G) {
+    case 4: return by_slots(std::integral_constant<int, 4>{});
+    case 8: return by_slots(std::integral_constant<int, 8>{});
+    case 16: return by_slots(std::integral_constant<int, 16>{});
+    case 32: return by_slots(std::integral_constant<int, 32>{});
+    default: break;
+  }
+  // other head counts: two launches
+  token_alpha_kernel<<<dim3((S + 255) / 256, P.units), 256, 0, st>>>(logits, stats, n_tchunks, block_ids, K_b, ctx_lens,
+                                                                     P.H_kv, P.G, P.B, P.T, keys, kinfo);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
   auto go = [&](auto kern) {
     const hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(kern), lds);
     if (e != hipSuccess) return e;
