@@ -119,6 +119,10 @@ def lib() -> ctypes.CDLL:
 # marshalling helpers
 # ----------------------------------------------------------------------------
 
+# Addresses are passed as plain ints: ctypes converts them by the entry
+# points' argtypes, and building c_void_p objects (and a torch Stream for the
+# default stream) took most of a call's 7 us of marshalling.
+
 def _ptr(t: Optional[torch.Tensor], what: str, device: bool = True):
     if t is None:
         return None
@@ -128,14 +132,18 @@ def _ptr(t: Optional[torch.Tensor], what: str, device: bool = True):
         raise ValueError(f"{what}: tensor must be contiguous")
     if device and not t.is_cuda:
         raise ValueError(f"{what}: tensor must live on the GPU")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
-def _stream(stream) -> ctypes.c_void_p:
+_current_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
+def _stream(stream) -> int:
     if stream is None:
+        if _current_raw_stream is not None:
+            return _current_raw_stream(torch.cuda.current_device())
         stream = torch.cuda.current_stream()
-    handle = stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
-    return ctypes.c_void_p(handle)
+    return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
 
 def _check(status: int, where: str) -> None:
@@ -291,16 +299,27 @@ def sparse_decode_args(layout, q, kv: KV, ctx_lens, kmax, kmin, codes, qparams, 
     return args, (opts, ev_arr, view, layout)
 
 
+_plain_opts: dict = {}  # (attn_splits, mode) -> DecodeOpts without events, never changed once made
+
+
 def _decode_opts(attn_splits, stage_events, mode):
+    if stage_events is None:
+        key = (int(attn_splits), int(mode))
+        opts = _plain_opts.get(key)
+        if opts is None:
+            opts = DecodeOpts()
+            opts.attn_splits = int(attn_splits)
+            opts.mode = int(mode)
+            if len(_plain_opts) < 256:
+                _plain_opts[key] = opts
+        return opts, None
     opts = DecodeOpts()
     opts.attn_splits = int(attn_splits)
     opts.mode = int(mode)
-    ev_arr = None
-    if stage_events is not None:
-        if len(stage_events) != NUM_STAGE_EVENTS:
-            raise ValueError(f"stage_events must hold {NUM_STAGE_EVENTS} events")
-        ev_arr = (ctypes.c_void_p * NUM_STAGE_EVENTS)(*[ctypes.c_void_p(int(e)) for e in stage_events])
-        opts.stage_events = ctypes.cast(ev_arr, ctypes.c_void_p)
+    if len(stage_events) != NUM_STAGE_EVENTS:
+        raise ValueError(f"stage_events must hold {NUM_STAGE_EVENTS} events")
+    ev_arr = (ctypes.c_void_p * NUM_STAGE_EVENTS)(*[ctypes.c_void_p(int(e)) for e in stage_events])
+    opts.stage_events = ctypes.cast(ev_arr, ctypes.c_void_p)
     return opts, ev_arr
 
 
