@@ -30,6 +30,7 @@ constexpr int kDsNW = kDsThreads / 64;
 constexpr int kDsMaxDc = 256;
 constexpr int kDsTopkThreads = 1024;
 constexpr int kDsListCap = 16384;  // keys in play (or candidates) kept in LDS
+constexpr int kDsMaskGroups = 4096;  // groups of 64 keys whose candidate masks are in LDS at a time
 constexpr int kDsHistWords = 260;  // per unit: 256 bucket counts, the key bound, padding
 
 // Bucket counts of a unit's keys: bucket b holds the keys with key >>
@@ -712,12 +713,16 @@ __global__ __launch_bounds__(kDsThreads) void ds_score_kernel(
 }
 
 // One work-group per unit.  With the bucket counts of pass 1 the bucket of the
-// K_t-th key is known at once; one ordered pass over the keys (tiles of 16 per
-// thread, the next tile requested before the last is compacted) lists the
-// positions of the keys at or above its lower end, and the selection finishes
-// on those keys in registers: 60 -> 27 us at 128 units of 73k keys.  Without
-// counts, where every key is selected, where the bucket is the lowest (it also
-// holds everything below 32 octaves) or where more candidates than
+// K_t-th key is known at once; one pass over the keys (16 per thread, the next
+// 16 requested before the last are compacted) lists the positions of the keys
+// at or above its lower end in order, and the selection finishes on those keys
+// in registers.  The pass has no barrier: a ballot per 64 keys leaves their
+// candidate mask in LDS, and once per 262144 keys each thread expands the masks
+// of four groups at most behind one prefix sum.  At 128 units of 73k keys: 60 us
+// for a radix pass at a time, 27 with an ordered compaction (two barriers) per
+// 16384 keys, 20.7 so; 32 keys per thread in flight: 21-23.
+// Without counts, where every key is selected, where the bucket is the lowest
+// (it also holds everything below 32 octaves) or where more candidates than
 // kDsListCap remain, the keys are streamed once per radix pass.
 template <int EPT>
 __device__ inline void ds_select_list(const uint32_t* keys, const int32_t* list, int cnt, int K_t, int32_t* out,
@@ -747,7 +752,8 @@ __global__ __launch_bounds__(kDsTopkThreads) void ds_topk_kernel(const uint32_t*
   extern __shared__ uint32_t smem[];
   uint32_t* scratch = smem;
   uint32_t* list = smem + topk_scratch_words(NT);
-  const int unit = blockIdx.x, tid = threadIdx.x;
+  const int unit = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
+  const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
   if (arrive && tid == 0) arrive[unit] = 0u;
   int n = ctx_lens[unit / H_kv];
   n = n < 0 ? 0 : (n > T ? T : n);
@@ -755,14 +761,14 @@ __global__ __launch_bounds__(kDsTopkThreads) void ds_topk_kernel(const uint32_t*
   int32_t* out = token_ids + size_t(unit) * K_t;
   if (hist && n > K_t) {
     const uint32_t* h = hist + size_t(unit) * kDsHistWords;
+    // group j of wave w in batch t: positions t TILE + (16 w + j) 64 + lane
     uint32_t kr[EPT];
     auto request = [&](int t) {
 #pragma unroll
-      for (int j = 0; j < EPT; ++j) kr[j] = uk[min(t * TILE + tid + j * NT, n - 1)];
+      for (int j = 0; j < EPT; ++j) kr[j] = uk[min(t * TILE + (wid * EPT + j) * 64 + lane, n - 1)];
     };
     request(0);
     // the bucket: lane L of every wave holds buckets 255 - 4L .. 252 - 4L
-    const int lane = tid & 63;
     const uint4 c = *reinterpret_cast<const uint4*>(h + 252 - 4 * lane);
     const uint32_t bound = h[256];
     const uint32_t c0 = c.w, c1 = c0 + c.z, c2 = c1 + c.y, c3 = c2 + c.x;
@@ -779,19 +785,50 @@ __global__ __launch_bounds__(kDsTopkThreads) void ds_topk_kernel(const uint32_t*
     const int cnt = int(above + bucket);
     if (digit > 0 && cnt <= kDsListCap) {
       const uint32_t lowest = uint32_t(int(bound >> kTopkSpreadShift) - 254 + digit) << kTopkSpreadShift;
-      uint32_t* misc = scratch + align4w_c(kTopkPasses * kTopkHistWords);
-      uint32_t* cg = misc + 64;
-      uint32_t* ce = cg + kTopkMaxEPT * kTopkMaxNW;
+      uint32_t* wsum = scratch + align4w_c(kTopkPasses * kTopkHistWords);
+      uint2* masks = reinterpret_cast<uint2*>(list + kDsListCap);
       topk_prepare<NT>(scratch);
       int base = 0;
-      for (int t = 0; t * TILE < n; ++t) {
-        uint32_t cur[EPT];
+      for (int t0 = 0; t0 * TILE < n; t0 += kDsMaskGroups / (EPT * NT / 64)) {
+        const int end = min(n, t0 * TILE + kDsMaskGroups * 64);
+        for (int t = t0; t * TILE < end; ++t) {
+          uint32_t mlo = 0u, mhi = 0u;
+          const int p0 = t * TILE + wid * EPT * 64;
 #pragma unroll
-        for (int j = 0; j < EPT; ++j) cur[j] = t * TILE + tid + j * NT < n ? kr[j] : kInvalidKey;
-        if ((t + 1) * TILE < n) request(t + 1);
-        base += topk_compact_impl<NT, EPT, false>(cur, lowest - 1u, 0, base, 0, reinterpret_cast<int32_t*>(list), nullptr,
-                                                  [=](int, int p) { return int32_t(t * TILE + p); }, cg, ce).x;
-        __syncthreads();  // cg is rewritten by the next tile; the list is complete after the last
+          for (int j = 0; j < EPT; ++j) {
+            const int left = n - (p0 + j * 64);  // keys of the group (uniform)
+            const uint64_t m = __ballot(kr[j] >= lowest) & (left >= 64 ? ~0ull : (left > 0 ? (1ull << left) - 1ull : 0ull));
+            mlo = lane == j ? uint32_t(m) : mlo;
+            mhi = lane == j ? uint32_t(m >> 32) : mhi;
+          }
+          if ((t + 1) * TILE < n) request(t + 1);
+          if (lane < EPT) masks[(t - t0) * (TILE / 64) + wid * EPT + lane] = make_uint2(mlo, mhi);
+        }
+        __syncthreads();
+        const int groups = (end - t0 * TILE + 63) / 64, per = (groups + NT - 1) / NT;
+        uint64_t m[kDsMaskGroups / NT];
+        int c = 0;
+#pragma unroll
+        for (int i = 0; i < kDsMaskGroups / NT; ++i) {
+          const int g = tid * per + i;
+          const bool ok = i < per && g < groups;
+          const uint2 w = masks[ok ? g : 0];
+          m[i] = ok ? uint64_t(w.y) << 32 | w.x : 0ull;
+          c += __popcll(m[i]);
+        }
+        const uint32_t incl_c = wave_incl_scan_u32(uint32_t(c));
+        if (lane == 63) wsum[wid] = incl_c;
+        __syncthreads();
+        const uint32_t ws = wsum[lane & 15];
+        const uint32_t wincl = wave_incl_scan_u32(lane < NT / 64 ? ws : 0u);
+        int off = base + int(incl_c) - c + (wid ? __builtin_amdgcn_readlane(int(wincl), wid - 1) : 0);
+        base += __builtin_amdgcn_readlane(int(wincl), NT / 64 - 1);
+#pragma unroll
+        for (int i = 0; i < kDsMaskGroups / NT; ++i) {
+          const int p = t0 * TILE + (tid * per + i) * 64;
+          for (uint64_t w = m[i]; w; w &= w - 1) list[off++] = uint32_t(p + __builtin_ctzll(w));
+        }
+        __syncthreads();  // the masks are rewritten by the next round; the list is complete after the last
       }
       const TopkStart start{lowest, K_t - int(above), int(bucket)};
       const int32_t* pos = reinterpret_cast<const int32_t*>(list);
@@ -909,7 +946,7 @@ hipError_t launch_token_select_dense(const Problem& P, const void* q, const uint
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  const size_t lds = (size_t(topk_scratch_words(kDsTopkThreads)) + kDsListCap) * sizeof(uint32_t);
+  const size_t lds = (size_t(topk_scratch_words(kDsTopkThreads)) + kDsListCap + 2 * kDsMaskGroups) * sizeof(uint32_t);
   e = allow_dynamic_lds(reinterpret_cast<const void*>(ds_topk_kernel), lds);
   if (e != hipSuccess) return e;
   ds_topk_kernel<<<P.units, kDsTopkThreads, lds, st>>>(keys, hist, ctx_lens, P.H_kv, P.T, K_t, token_ids, arrive);

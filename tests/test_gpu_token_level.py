@@ -72,6 +72,15 @@ def _select(layout, q, K, V, n, ch, codes, qp, k_t, noalloc=False):
 @pytest.mark.parametrize("lens,k_t", [((1, 63, 1025), 1), ((4095, 4097, 300), 500), ((16383, 16385, 9000), 2048)])
 @pytest.mark.parametrize("G,d,d_c,dtype,mla", CASES)
 def test_selected_tokens(G, d, d_c, dtype, mla, lens, k_t):
+    check_selected_tokens(G, d, d_c, dtype, mla, lens, k_t)
+
+
+# the selection keeps the candidate masks of 262144 tokens at a time
+def test_selected_tokens_of_long_contexts():
+    check_selected_tokens(*CASES[2], (262143, 262145, 300000), 2048)
+
+
+def check_selected_tokens(G, d, d_c, dtype, mla, lens, k_t):
     a = _setup(G, d, d_c, dtype, mla, lens, 11 * G + d_c)
     layout, q, K, V, n, ch, codes, qp = a
     tids = _select(*a, k_t).cpu()
