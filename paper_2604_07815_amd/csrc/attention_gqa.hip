@@ -256,8 +256,10 @@ __global__ __launch_bounds__(256) void attn_gqa_chunk_kernel(
   attn_gqa_body<E, D, G, 1>(q, Kp, Vp, slot_map, n_slots, tl, ctx_lens, H_q, H_kv, T, B, m_max, K_t, tpw, sigma, so, err);
 }
 
+// (8 heads of 64 fit five times into a compute unit's LDS; without the bound the
+// registers of the merge leave four: 128 units of 8192 tokens 64.4 us, 63.3 so)
 template <int D, int G, int NW, int TPWV, bool WHOLE>
-__global__ __launch_bounds__(64 * NW) void attn_gqa_mfma_kernel(
+__global__ __launch_bounds__(64 * NW, NW == kAttnNW && D == 64 && G == 8 ? 5 : 1) void attn_gqa_mfma_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ Kp, const uint16_t* __restrict__ Vp,
     const int32_t* __restrict__ slot_map, int64_t n_slots, const TokenList tl,
     const int32_t* __restrict__ ctx_lens, int H_q, int H_kv, int T, int B, int m_max, int K_t, int tpw,
@@ -297,13 +299,19 @@ static int mfma_wgs_per_cu_g(int G) {
 }
 
 // The unit's last work-group merges the splits where a thread of it has one
-// pair of output columns and the partials are no more than a work-group reads
-// in the time of a launch.  Against the merge kernel (whole step, 8 to 248
-// units, 256 to 2048 tokens, D = 64 and 128): 0.8 to 1.8 us less with 1, 2 and
-// 4 heads (b = 1, 48k: 33.4 -> 32.1 us) and 8 heads of 64; with 8 heads of 128
-// between 1.2 less and 1.0 more, so those keep the kernel.
+// pair of output columns, the partials are no more than a work-group reads in
+// the time of a launch, the launch is one round of resident work-groups (the
+// wait for its partial holds a work-group's place) and it is short: the launch
+// saved is then worth more than the waits.  Against the merge kernel (whole
+// step): 0.8 to 1.8 us less with 1, 2 and 4 heads (b = 1, 48k: 33.4 -> 32.1 us)
+// and 8 heads of 64 up to 2^18 tokens over all units (128 units of 2048 tokens:
+// 64.6 -> 63.4, 32 of 8192: 39.5 -> 38.4); 160 units of 2048 tokens 0.4 less to
+// 0.4 more, 64 of 8192 0.5 more, 128 of 8192 1.0 more, and in several rounds
+// (256 units of 8192 tokens) 5 to 18 us more.  With 8 heads of 128 between 1.2
+// less and 1.0 more, so those keep the kernel.
 constexpr int kFoldColumns = 512;
 constexpr long kFoldFloats = 32768;
+constexpr long kFoldTokens = 1 << 18;
 
 constexpr int kWideMinTokens = 768;  // tokens per 12-wave split work-group worth its prologue
 
@@ -364,8 +372,10 @@ static bool launch_t(const Problem& P, const void* q, const KvView& kv, const To
   dim3 grid(nsplit, P.units);
   int tpw = (K_t + nsplit - 1) / nsplit;
   SplitOut so = so_in;
-  if (G * D > kFoldColumns || long(nsplit) * G * D > kFoldFloats) so.arrive = nullptr;
+  if (G * D > kFoldColumns || long(nsplit) * G * D > kFoldFloats || long(P.units) * K_t > kFoldTokens)
+    so.arrive = nullptr;
   if constexpr (E::kIsBf16) {
+    if (long(P.units) * nsplit > long(device_cus()) * mfma_wgs_per_cu<D, G>()) so.arrive = nullptr;
     if (gqa_use_wide(P, K_t, nsplit, device_cus())) {
       constexpr int wstep = 16 * kWholeNW;
       tpw = (tpw + wstep - 1) / wstep * wstep;
