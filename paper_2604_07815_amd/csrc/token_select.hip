@@ -6,14 +6,17 @@
 // slot order is token order, so lowest-slot tie-breaking is lowest-position
 // tie-breaking.
 //
-// token_score_kernel: per slot and head, l = sigma * q~_h . dequant(code_j).
+// token_score_*_kernel: per slot and head, l = sigma * q~_h . dequant(code_j)
+//   (mfma: bf16 with 16 or 32 heads; lane: bf16 up to 8 heads; row: 1, 2, 4 or
+//   8 heads on the vector units, the fp32 layout; token_score_kernel: the rest).
 //   With dequant = min + code*scale per 32-channel group this is
 //   sigma * sum_grp (min_grp * sum_c q~_hc + scale_grp * sum_c q~_hc code_c):
 //   the integer codes enter the dot product directly.  Also emits each
 //   work-group's per-head (max, sum exp) of its slots.
-// token_alpha_kernel: per-head normalisers over all candidates, then
-//   alpha_j = (1/G) sum_h exp(l_hj - m_h) / Z_h as an orderable key.
-// token_topk_kernel: the K_t largest alpha, ascending token positions.
+// token_alpha_topk_kernel: per-head normalisers over all candidates, then
+//   alpha_j = (1/G) sum_h exp(l_hj - m_h) / Z_h as an orderable key, and the
+//   K_t largest alpha as ascending token positions (4 or 8 heads; 16 or 32 with
+//   up to 1024 candidates; otherwise token_alpha_kernel(_g), token_topk_kernel).
 #include <type_traits>
 
 #include "token_common.hpp"
@@ -161,7 +164,7 @@ __device__ inline void write_chunk_stats(const float (*s_red)[NH][2], int G, flo
 // then q~ and the slot's rows) with one barrier, a row is dequantised in
 // registers and meets the heads' q~ of a channel in one LDS read.  The sums of
 // min and scale parts are not kept apart: sum_c q~_c (min + scale code_c) with
-// each term centred rounds less.  8 heads x 4096 tokens, K_b = 8: 9.4 -> 4 us.
+// each term centred rounds less.  2 units of 4 heads, 512 slots: 9.4 -> 4 us.
 template <class E, int G>
 __global__ __launch_bounds__(256) void token_score_row_kernel(
     const typename E::T* __restrict__ q, const uint8_t* __restrict__ codes, const float* __restrict__ qparams,
@@ -248,7 +251,7 @@ __global__ __launch_bounds__(256) void token_score_row_kernel(
 // bf16, G <= 4 HS, d_c = 32 NGR, where the fused kernel does not apply (more
 // than four heads or one group, larger budgets): the same two rounds of
 // requests, the contraction of a lane's slot on the matrix cores (lane_dots).
-// 32 units of 8 heads, d_c = 64, 4096 slots: 18.3 -> 6 us.
+// 32 units of 8 heads, d_c = 64, 4096 slots: 18.3 -> 7.1 us.
 template <int HS, int NGR>
 __global__ __launch_bounds__(256) void token_score_lane_kernel(
     const uint16_t* __restrict__ q, const uint8_t* __restrict__ codes, const float* __restrict__ qparams,
@@ -610,19 +613,101 @@ __global__ __launch_bounds__(256) void token_alpha_kernel(
   }
 }
 
-// Alpha and the top-K_t in one launch, for G = 4, 8, 16, 32: a work-group of
-// 1024 threads computes the keys of 1024 slots, stores them past the L2s (as
-// SplitOut's partials) and counts itself in; the unit's last one reads all of
-// them back into registers and selects, from bounds it knows (each exponential
-// is <= 1, so alpha is at most (1/G) sum_h 1/Z_h summed in the key loop's
-// order).  A latency chain: every request of a work-group leaves at once
-// before the first is used (statistics, block-list entries, the slot's G
-// logits; unconditional loads at clamped addresses).  With one work-group per
-// unit it is a single pass.  Against an alpha and a top-K_t launch: 2 units of
-// 512 slots 6.6 -> 4.8 us, 32 units of 8 heads and 4096 slots 9.9 -> 9.4, MLA
-// (8 units of 32 heads, 8192 slots) 13.4 either way: storing, counting and
-// reading back cost what a launch does, and spreading a slot's heads over four
-// threads changed nothing (14.0).
+// token_alpha_kernel with the head count fixed at compile time, for a grid
+// of one slot per thread: 256/G lanes combine each head's work-group
+// statistics, and every request of a work-group leaves at once before the
+// first is used (its lanes' statistics, the block-list entries of its slots
+// and of the unit information, the slots' G logits; unconditional loads at
+// clamped addresses), so the kernel waits for one memory round trip.
+template <int G>
+__global__ __launch_bounds__(256) void token_alpha_kernel_g(
+    const float* __restrict__ logits, const float* __restrict__ stats, int n_tchunks,
+    const int32_t* __restrict__ block_ids, int K_b, const int32_t* __restrict__ ctx_lens, int H_kv, int B, int T,
+    uint32_t* __restrict__ keys, uint32_t* __restrict__ kinfo) {
+  constexpr int TPH = 256 / G;  // lanes per head (a power of two)
+  constexpr int kC = 8;         // statistics chunks per lane requested together
+  __shared__ float s_m[G], s_iz[G];
+  __shared__ uint32_t s_cnt[4];
+  const int unit = blockIdx.y, tid = threadIdx.x;
+  const int s = unit / H_kv;
+  const int S = K_b * B;
+  const int h = tid / TPH, j = tid % TPH;
+  const float2* st = reinterpret_cast<const float2*>(stats) + size_t(unit) * n_tchunks * G;
+  const int32_t* bl = block_ids + size_t(unit) * K_b;
+  const float* lg = logits + size_t(unit) * G * S;
+  const int slot = blockIdx.x * 256 + tid, sl = min(slot, S - 1);
+  float2 sv[kC];
+#pragma unroll
+  for (int c = 0; c < kC; ++c) sv[c] = st[size_t(min(j + c * TPH, n_tchunks - 1)) * G + h];
+  __builtin_amdgcn_sched_barrier(0);
+  const int b_slot = bl[tok_block(sl, B)];
+  const int b_first = bl[min(tid, K_b - 1)];
+  float v[G];
+#pragma unroll
+  for (int hh = 0; hh < G; ++hh) v[hh] = lg[size_t(hh) * S + sl];
+  __builtin_amdgcn_sched_barrier(0);
+  int n = ctx_lens[s];
+  n = n < 0 ? 0 : (n > T ? T : n);
+  const int m = (n + B - 1) / B;
+  {
+    // chunks j, j + TPH, ... in ascending order, then the lanes' tree (the
+    // requested entries are used through selects, not branches, so that
+    // no load is sunk into a branch; adding +0 leaves Z >= +0 unchanged)
+    float M = -INFINITY;
+#pragma unroll
+    for (int c = 0; c < kC; ++c) M = fmaxf(M, j + c * TPH < n_tchunks ? sv[c].x : -INFINITY);
+    for (int c = j + kC * TPH; c < n_tchunks; c += TPH) M = fmaxf(M, st[size_t(c) * G + h].x);
+#pragma unroll
+    for (int o = TPH / 2; o > 0; o >>= 1) M = fmaxf(M, __shfl_xor(M, o, 64));
+    float Z = 0.f;
+    if (M != -INFINITY) {
+#pragma unroll
+      for (int c = 0; c < kC; ++c) {
+        const bool ok = j + c * TPH < n_tchunks && sv[c].x != -INFINITY;
+        Z += ok ? sv[c].y * __expf(sv[c].x - M) : 0.f;
+      }
+      for (int c = j + kC * TPH; c < n_tchunks; c += TPH) {
+        const float2 e = st[size_t(c) * G + h];
+        if (e.x != -INFINITY) Z += e.y * __expf(e.x - M);
+      }
+    }
+#pragma unroll
+    for (int o = TPH / 2; o > 0; o >>= 1) Z += __shfl_xor(Z, o, 64);
+    if (j == 0) {
+      s_m[h] = M;
+      s_iz[h] = Z > 0.f ? 1.0f / Z : 0.f;
+    }
+  }
+  __syncthreads();
+  const float invG = 1.0f / float(G);
+  if (blockIdx.x == 0) write_unit_info(bl, b_first, K_b, B, m, n, s_iz, G, invG, kinfo, unit, s_cnt);
+  if (slot < S) {
+    const int t = b_slot * B + tok_offset(slot, B);
+    uint32_t key = kInvalidKey;
+    if (b_slot >= 0 && b_slot < m && t < n) {
+      float a = 0.f;
+#pragma unroll
+      for (int hh = 0; hh < G; ++hh) a += __expf(v[hh] - s_m[hh]) * s_iz[hh];
+      key = alpha_key(a * invG);
+    }
+    keys[size_t(unit) * S + slot] = key;
+  }
+}
+
+// Alpha and the top-K_t in one launch: a work-group of 1024 threads computes the
+// keys of 1024 slots, stores them past the L2s (as SplitOut's partials) and
+// counts itself in; the unit's last one reads all of them back into registers
+// and selects, from bounds it knows (each exponential is <= 1, so alpha is at
+// most (1/G) sum_h 1/Z_h summed in the key loop's order).  A latency chain: every
+// request of a work-group leaves at once before the first is used (statistics,
+// block-list entries, the slot's G logits; unconditional loads at clamped
+// addresses).  With one work-group per unit it is a single pass.  Against an
+// alpha and a top-K_t launch: 2 units of 512 slots 6.6 -> 4.8 us, 32 units of 8
+// heads and 4096 slots 9.9 -> 9.4.  Storing, counting and reading back cost what
+// a launch does, and with 16 or 32 heads more (32 heads, whole step of 8 units
+// and 8192 slots 53.4 us against 52.7 in two launches, 2 units and 6400 slots
+// 41.8 against 40.5), so those take it only in the single-pass form; spreading a
+// slot's heads over four threads changed nothing.
 template <int G, int EPT>
 __global__ __launch_bounds__(1024) void token_alpha_topk_kernel(
     const float* __restrict__ logits, const float* __restrict__ stats, int n_tchunks,
@@ -858,16 +943,20 @@ hipError_t launch_token_alpha_topk(const Problem& P, const float* logits, const 
     if (ept <= 8) return one(token_alpha_topk_kernel<G, 8>);
     return one(token_alpha_topk_kernel<G, 16>);
   };
-  switch (P.G) {
-    case 4: return by_slots(std::integral_constant<int, 4>{});
-    case 8: return by_slots(std::integral_constant<int, 8>{});
-    case 16: return by_slots(std::integral_constant<int, 16>{});
-    case 32: return by_slots(std::integral_constant<int, 32>{});
-    default: break;
-  }
-  // other head counts: two launches
-  token_alpha_kernel<<<dim3((S + 255) / 256, P.units), 256, 0, st>>>(logits, stats, n_tchunks, block_ids, K_b, ctx_lens,
-                                                                     P.H_kv, P.G, P.B, P.T, keys, kinfo);
+  if (P.G == 4) return by_slots(std::integral_constant<int, 4>{});
+  if (P.G == 8) return by_slots(std::integral_constant<int, 8>{});
+  if (P.G == 16 && ept == 1) return one(token_alpha_topk_kernel<16, 1>);
+  if (P.G == 32 && ept == 1) return one(token_alpha_topk_kernel<32, 1>);
+  // two launches
+  const dim3 grid((S + 255) / 256, P.units);
+  auto alpha = [&](auto kern) {
+    kern<<<grid, 256, 0, st>>>(logits, stats, n_tchunks, block_ids, K_b, ctx_lens, P.H_kv, P.B, P.T, keys, kinfo);
+  };
+  if (P.G == 16) alpha(token_alpha_kernel_g<16>);
+  else if (P.G == 32) alpha(token_alpha_kernel_g<32>);
+  else
+    token_alpha_kernel<<<grid, 256, 0, st>>>(logits, stats, n_tchunks, block_ids, K_b, ctx_lens, P.H_kv, P.G, P.B, P.T,
+                                             keys, kinfo);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   auto go = [&](auto kern) {
