@@ -37,8 +37,8 @@
 // x 65536 tokens, 604 MB, attention and merge): 112 us, 5.4 TB/s; 243 us for
 // 32-token chunks with the queries in LDS (one work-group per compute unit),
 // five barriers per chunk and gathers of 64 rows' single pieces, each its own
-// cache line.  16 heads ran on the vector kernel before (b = 2 step of 500
-// tokens: 78 -> 45 us).
+// cache line.  16 heads ran on the vector kernel before: a two-level step
+// of 1-2 sequences of 16 heads took 83-86 us with it, 36 with this one.
 #include "attn_common.hpp"
 
 namespace tls {
@@ -307,19 +307,24 @@ int mla_mfma_tokens_per_split() { return kMlaMaxTPW; }
 // and merge, 32 heads, against the former one work-group per compute unit
 // (b units of K tokens, us): 8 x 2048: 16 splits 18.7, 32 splits 22.3; 16 x
 // 2048: 8 splits 23.4, 16 splits 23.9; 8 x 8192: 32 splits 30.3, 16 splits
-// 31.5, 64 splits 33.8.
+// 31.5, 64 splits 33.8.  With 32 heads a split may be as short as 32 tokens,
+// whose rows take five eighths of a chunk's time to arrive: few units with few
+// tokens (whole two-level step, 64-token splits against these): 1 x 500 39.9 ->
+// 38.5, 2 x 500 40.9 -> 39.4, 3 x 300 39.7 -> 38.8 us.
 int mla_mfma_splits(const Problem& P, int K_t) {
   constexpr int kChunk = 64;
   const long chunk_cost = 73 * 32 / P.G;  // in partials of one split and unit
   const int need = (K_t + kMlaMaxTPW - 1) / kMlaMaxTPW;
+  const int ct = P.G == 32 ? kChunk / 2 : kChunk;  // the smallest split
   int max_ns = device_cus() / P.units;
-  if (max_ns > (K_t + kChunk - 1) / kChunk) max_ns = (K_t + kChunk - 1) / kChunk;
+  if (max_ns > (K_t + ct - 1) / ct) max_ns = (K_t + ct - 1) / ct;
   if (max_ns > kMaxSplits) max_ns = kMaxSplits;
   int best = need;
   long best_cost = -1;
   for (int ns = need; ns <= max_ns; ++ns) {
-    const long chunks = ((K_t + ns - 1) / ns + kChunk - 1) / kChunk;
-    const long cost = chunks * chunk_cost + long(ns) * P.units;
+    const int tokens = (K_t + ns - 1) / ns;
+    const long chain = tokens <= kChunk / 2 ? chunk_cost * 5 / 8 : (tokens + kChunk - 1) / kChunk * chunk_cost;
+    const long cost = chain + long(ns) * P.units;
     if (best_cost < 0 || cost < best_cost) {
       best_cost = cost;
       best = ns;
@@ -344,13 +349,14 @@ static hipError_t launch_mla_t(const Problem& P, const void* q, const KvView& kv
 // 64-token chunks where every work-group has a compute unit to itself (3
 // units of 65536 tokens in 64 splits: 53 us against 59), two work-groups of
 // 32-token chunks per compute unit where there are more (8 such units: 113 us
-// against 122).  16 heads have half the waves per token tile and
+// against 122), and 32-token chunks for splits that have no more tokens (see
+// mla_mfma_splits).  16 heads have half the waves per token tile and
 // always take 64 tokens.
 hipError_t launch_attention_mla_mfma(const Problem& P, const void* q, const KvView& kv, const TokenList& tl,
                                      const int32_t* ctx_lens, int K_t, int nsplit, float* po, float* plse,
                                      uint32_t* err, hipStream_t st) {
   if (P.G == 16) return launch_mla_t<1, 4>(P, q, kv, tl, ctx_lens, K_t, nsplit, po, plse, err, st);
-  if (long(P.units) * nsplit <= device_cus())
+  if (long(P.units) * nsplit <= device_cus() && K_t > 32 * nsplit)
     return launch_mla_t<2, 4>(P, q, kv, tl, ctx_lens, K_t, nsplit, po, plse, err, st);
   return launch_mla_t<2, 2>(P, q, kv, tl, ctx_lens, K_t, nsplit, po, plse, err, st);
 }
