@@ -89,7 +89,9 @@ enum {
 /* Number of events tls_decode_opts.stage_events must hold: one before each
  * of the seven stages (block score, block top-k, token score, token
  * normalisation, token top-k, attention, split merge) and one after the
- * last. */
+ * last.  A stage that is part of the next one's launch (the normalisation
+ * in the token top-k) or of the one before (the merge in the attention)
+ * shows as an empty interval. */
 #define TLS_NUM_STAGE_EVENTS 8
 
 typedef struct tls_layout {

@@ -28,6 +28,12 @@ CASES = {
                                            seed=142),
     "mla_bf16": synth.config("mla").replace(batch=2, ctx_lo=600, ctx_hi=1100, clusters=1, k_b=6, k_t=100,
                                             seed=143),
+    # key rows of 128 and 256 bytes
+    "gqa_d64_bf16": synth.config("qwen3_gqa_48k").replace(batch=2, h_q=8, h_kv=2, d_qk=64, d_v=64, ctx_lo=500,
+                                                          ctx_hi=1100, clusters=1, k_b=6, k_t=100, seed=146),
+    "gqa_d64_f32": synth.config("qwen3_gqa_48k").replace(dtype="f32", batch=2, h_q=8, h_kv=2, d_qk=64, d_v=64,
+                                                         ctx_lo=500, ctx_hi=1100, clusters=1, k_b=6, k_t=100,
+                                                         seed=147),
     # V rows of 72 bytes (not a multiple of 16): the element-wise V copy
     "odd_dv_bf16": synth.config("toy").replace(dtype="bf16", batch=2, h_q=4, h_kv=2, d_v=36, ctx_lo=200, ctx_hi=333,
                                                clusters=1, k_b=2, k_t=32, seed=145),
