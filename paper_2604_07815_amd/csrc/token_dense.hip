@@ -722,7 +722,10 @@ __global__ __launch_bounds__(kDsThreads) void ds_score_kernel(
 // for a radix pass at a time, 27 with an ordered compaction (two barriers) per
 // 16384 keys, 20.7 so; 32 keys per thread in flight: 21-23.
 // Without counts, where every key is selected, where the bucket is the lowest
-// (it also holds everything below 32 octaves) or where more candidates than
+// (it also holds everything below 32 octaves) or the highest (it also holds
+// everything above: a key exceeds the bound by the rounding of its logits,
+// which pass 1 computes without pass 0's rounding of the product with sigma,
+// i.e. by octaves where they are above 2^22), or where more candidates than
 // kDsListCap remain, the keys are streamed once per radix pass.
 template <int EPT>
 __device__ inline void ds_select_list(const uint32_t* keys, const int32_t* list, int cnt, int K_t, int32_t* out,
@@ -783,7 +786,7 @@ __global__ __launch_bounds__(kDsTopkThreads) void ds_topk_kernel(const uint32_t*
     const uint32_t above = uint32_t(__builtin_amdgcn_readlane(int(before), src));
     const uint32_t bucket = uint32_t(__builtin_amdgcn_readlane(int(here), src));
     const int cnt = int(above + bucket);
-    if (digit > 0 && cnt <= kDsListCap) {
+    if (digit > 0 && digit < 255 && cnt <= kDsListCap) {
       const uint32_t lowest = uint32_t(int(bound >> kTopkSpreadShift) - 254 + digit) << kTopkSpreadShift;
       uint32_t* wsum = scratch + align4w_c(kTopkPasses * kTopkHistWords);
       uint2* masks = reinterpret_cast<uint2*>(list + kDsListCap);

@@ -108,6 +108,20 @@ def test_equal_scores_take_the_lowest_positions(G, d, d_c, dtype, mla, noalloc):
     assert bool((tids == torch.arange(600, dtype=torch.int32)).all())
 
 
+@pytest.mark.parametrize("G,d,d_c,dtype,mla", [CASES[0], CASES[2], CASES[4], CASES[5], CASES[7]])
+def test_equal_scores_of_large_logits(G, d, d_c, dtype, mla):
+    """Equal rows and queries of 1e5 to 1e9: the rounding of a logit is then up to several octaves of its exponential,
+    so every key may lie above the bound that the second pass states.  Still the lowest positions, and no more."""
+    lens, k_t = (2000, 1500, 5000), 500
+    layout, q, K, V, n, ch, codes, qp = _setup(G, d, d_c, dtype, mla, lens, 9)
+    codes[:] = codes[:, :, :1].clone()
+    qp[:] = qp[:, :, :1].clone()
+    for k in range(12):
+        big = (q.float() * (1e5 * 2.37 ** k * (24 if mla else 1))).to(dtype)
+        tids = _select(layout, big, K, V, n, ch, codes, qp, k_t).cpu()
+        assert bool((tids == torch.arange(k_t, dtype=torch.int32)).all()), k
+
+
 SELECT = [
     # (G, d_qk, d_c, dtype): the two-level token stage where the fused kernel does not apply
     (8, 128, 32, torch.bfloat16), (8, 64, 64, torch.bfloat16), (8, 128, 128, torch.bfloat16),
