@@ -22,7 +22,9 @@
 //     over the token tiles, with two more barriers (always the first chunk,
 //     rarely a later one);
 //   * wave w owns output dims [512 w / NW, ...): O += P V by
-//     v_mfma_f32_16x16x32_bf16 over 32 tokens.  The two products agree on the
+//     v_mfma_f32_16x16x32_bf16 over 32 tokens, P rounded to bf16 for 32 heads
+//     and entered as three bf16 parts that hold all 24 bits of its fp32 value
+//     for 16 heads.  The two products agree on the
 //     order of the 32 tokens (4 lg + r of two token tiles), so that a lane's
 //     own scores are its A operand and two ds_read_b64_tr_b16 its B operand.
 // The work-group writes normalised partials and their log-sum-exp; the merge
@@ -37,8 +39,13 @@
 // x 65536 tokens, 604 MB, attention and merge): 112 us, 5.4 TB/s; 243 us for
 // 32-token chunks with the queries in LDS (one work-group per compute unit),
 // five barriers per chunk and gathers of 64 rows' single pieces, each its own
-// cache line.  16 heads ran on the vector kernel before: a two-level step
-// of 1-2 sequences of 16 heads took 83-86 us with it, 36 with this one.
+// cache line.  16 heads ran on the vector kernel before, with fp32
+// probabilities: a two-level step of 1, 16 and 48 sequences (2048 of 8192
+// tokens) took 85.8, 153 and 386 us with it, 42.4, 54.3 and 78.6 with this one.
+// Their three parts cost up to 1 us of that (42.7, 53.7, 77.4 with one bf16
+// part, whose error from 64 bits is 2.05e-3 in the 2-norm; 1.648e-3 with three,
+// as on the vector kernel, which is the rounding of the output).  32 heads
+// keep one part: 2.06e-3.
 #include "attn_common.hpp"
 
 namespace tls {
@@ -57,7 +64,9 @@ template <int HT, int TT>
 struct AttnMlaLds {
   static constexpr int CT = 16 * TT;
   alignas(16) uint4 kv[2][CT * kMlaPieces];
-  alignas(16) uint2 p[TT / 2][HT][64][2];  // [token tile pair][ht][lane][tile of the pair]
+  // bf16 parts of a probability: 16 heads leave the matrix cores room for all of fp32
+  static constexpr int PP = HT == 1 ? 3 : 1;
+  alignas(16) uint2 p[PP][TT / 2][HT][64][2];  // [part][token tile pair][ht][lane][tile of the pair]
   int src[kMlaMaxTPW];                     // row gathered for each entry
   uint64_t valid[kMlaMaxTPW / CT];         // valid entries of each chunk
   float cmax[TT][HT * 16], l[TT][HT * 16], sc[HT * 16], m[HT * 16];
@@ -76,6 +85,7 @@ __global__ __launch_bounds__(64 * HT * TT, 2) void attn_mla_mfma_kernel(
   constexpr int NG = kMlaPieces * CT / 64 / NW;  // gathers per wave per chunk
   constexpr int DW = kMlaDv / NW, NNT = DW / 16;  // output dims (tiles) per wave
   constexpr int KS = TT / 2;                      // 32-token steps of the second product
+  constexpr int PP = AttnMlaLds<HT, TT>::PP;
   constexpr float kLog2e = 1.4426950408889634f;
   constexpr float kRaise = 8.0f;
   static_assert(NG * NW * 64 == kMlaPieces * CT && DW % 64 == 0 && TT % 2 == 0, "tile geometry");
@@ -200,14 +210,24 @@ __global__ __launch_bounds__(64 * HT * TT, 2) void attn_mla_mfma_kernel(
     // probabilities against the maximum m, to this wave's half of the operand
     auto write_p = [&](const float m) {
       float ps = 0.f;
-      short pb[4];
+      short pb[PP][4];
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const float p = z[r] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(z[r] - m);
+        float p = z[r] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(z[r] - m);
         ps += p;
-        pb[r] = bf16_bits_rne(p);
+        if constexpr (PP == 1) {
+          pb[0][r] = bf16_bits_rne(p);
+        } else {  // eight leading bits at a time: every difference is exact, the last part is what is left
+#pragma unroll
+          for (int k = 0; k < PP; ++k) {
+            pb[k][r] = short(__float_as_uint(p) >> 16);
+            p -= __uint_as_float(__float_as_uint(p) & 0xffff0000u);
+          }
+        }
       }
-      lds.p[tt >> 1][ht][lane][tt & 1] = __builtin_bit_cast(uint2, i16x4_t{pb[0], pb[1], pb[2], pb[3]});
+#pragma unroll
+      for (int k = 0; k < PP; ++k)
+        lds.p[k][tt >> 1][ht][lane][tt & 1] = __builtin_bit_cast(uint2, i16x4_t{pb[k][0], pb[k][1], pb[k][2], pb[k][3]});
       return ps;
     };
     float ps = 0.f;
@@ -247,9 +267,11 @@ __global__ __launch_bounds__(64 * HT * TT, 2) void attn_mla_mfma_kernel(
     // O += P V for this wave's output dims
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
-      bf16x8_t pa[HT];
+      bf16x8_t pa[PP][HT];
 #pragma unroll
-      for (int a = 0; a < HT; ++a) pa[a] = *reinterpret_cast<const bf16x8_t*>(&lds.p[ks][a][lane][0]);
+      for (int k = 0; k < PP; ++k)
+#pragma unroll
+        for (int a = 0; a < HT; ++a) pa[k][a] = *reinterpret_cast<const bf16x8_t*>(&lds.p[k][ks][a][lane][0]);
       // V operand: rows ks*32 + 4lg + (t16 / 4) and 16 more, dims 16nt + 4 (t16 % 4) .. +4
       const int vz = (lg * 2 + (t16 >> 3)) & 7;  // the rows' swizzle
       const uint8_t* vrow = reinterpret_cast<const uint8_t*>(&lds.kv[b][(ks * 32 + lg * 4 + (t16 >> 2)) * kMlaPieces]);
@@ -262,7 +284,10 @@ __global__ __launch_bounds__(64 * HT * TT, 2) void attn_mla_mfma_kernel(
         const bf16x8_t vb = __builtin_bit_cast(
             bf16x8_t, __builtin_shufflevector(v0, v1, 0, 1, 2, 3, 4, 5, 6, 7));
 #pragma unroll
-        for (int a = 0; a < HT; ++a) acc[a][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pa[a], vb, acc[a][nt], 0, 0, 0);
+        for (int a = 0; a < HT; ++a)
+#pragma unroll
+          for (int k = PP - 1; k >= 0; --k)
+            acc[a][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pa[k][a], vb, acc[a][nt], 0, 0, 0);
       }
     }
   }

@@ -83,3 +83,25 @@ def test_rising_logits_raise_the_maximum(heads, splits):
     ids = torch.arange(1024).reshape(1, 1, -1).repeat(2, 1, 1).int()
     ids[1] = ids[1].flip(-1)
     _check(q, K, ids, *_decode(q, K, ids, splits))
+
+
+@pytest.mark.parametrize("k_t,splits,growing", [(33, 1, False), (500, 0, False), (1025, 0, False), (1024, 2, True)])
+def test_sixteen_heads_keep_fp32_probabilities(k_t, splits, growing):
+    """With 16 heads the probabilities enter the second product unrounded, so nothing but the output's own rounding
+    (2^-8 |o|) and fp32 errors is left: a logit is a sum of 576 products of magnitude sum |q k| / 24, each addition off
+    by 2^-24 of it in the worst case, and a weight by twice the largest logit error (its own and the normaliser's),
+    plus 2^-20 for the exponentials and the 32-bit sums."""
+    q, K = _inputs(16, 2, 40 + k_t, growing)
+    g = torch.Generator().manual_seed(k_t)
+    ids = torch.stack([torch.randperm(T, generator=g)[:k_t].sort().values for _ in range(2)]).reshape(2, 1, k_t).int()
+    out, _ = _decode(q, K, ids, splits)
+    for s in range(2):
+        k = K[s, 0][ids[s, 0].long()].double()
+        w = torch.softmax((q[s].double() @ k.T) / 24.0, -1)
+        o, mag = w @ k[:, :512], w @ k[:, :512].abs()
+        size = ((q[s].double().abs() @ k.abs().T) / 24.0).amax(-1, keepdim=True)
+        tol = 2.0 ** -8 * o.abs() + (2 * 576 * 2.0 ** -24 * size + 2.0 ** -20) * mag
+        err = (out[s].double() - o).abs()
+        assert bool((err <= tol).all()), (s, float((err / tol).max()))
+        if not growing:  # and nearly every value is the bf16 number nearest to the result
+            assert float((out[s] != o.to(torch.bfloat16)).double().mean()) < 0.01
