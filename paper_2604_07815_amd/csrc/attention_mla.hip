@@ -208,12 +208,13 @@ __global__ __launch_bounds__(64 * HT * TT, 2) void attn_mla_mfma_kernel(
       zmax = fmaxf(zmax, z[r]);
     }
     // probabilities against the maximum m, to this wave's half of the operand
+    // (m is -inf while every logit of the head is -inf or NaN: none counts)
     auto write_p = [&](const float m) {
       float ps = 0.f;
       short pb[PP][4];
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        float p = z[r] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(z[r] - m);
+        float p = z[r] == -INFINITY || m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(z[r] - m);
         ps += p;
         if constexpr (PP == 1) {
           pb[0][r] = bf16_bits_rne(p);
@@ -309,7 +310,12 @@ __global__ __launch_bounds__(64 * HT * TT, 2) void attn_mla_mfma_kernel(
       for (int v = 0; v < TT; ++v) L += lds.l[v][h];
       const float inv = L > 0.f ? 1.0f / L : 0.f;
 #pragma unroll
-      for (int nt = 0; nt < NNT; ++nt) po[(pbase + h) * kMlaDv + DW * w + 16 * nt + t16] = acc[a][nt][r] * inv;
+      for (int nt = 0; nt < NNT; ++nt) {
+        // (a sum that is NaN leaves its split out with 16 heads, as on the
+        // vector kernel, and makes the output NaN with 32)
+        const float o = acc[a][nt][r] * inv;
+        po[(pbase + h) * kMlaDv + DW * w + 16 * nt + t16] = HT == 1 && !(L > 0.f) ? 0.f : o;
+      }
     }
   if (tid < G) {
     float L = 0.f;

@@ -105,3 +105,27 @@ def test_sixteen_heads_keep_fp32_probabilities(k_t, splits, growing):
         assert bool((err <= tol).all()), (s, float((err / tol).max()))
         if not growing:  # and nearly every value is the bf16 number nearest to the result
             assert float((out[s] != o.to(torch.bfloat16)).double().mean()) < 0.01
+
+
+@pytest.mark.parametrize("heads", [16, 32])
+@pytest.mark.parametrize("k_t,splits", [(40, 1), (500, 0), (1024, 2)])
+def test_nan_query_head_attends_nothing(heads, k_t, splits):
+    """A head whose every logit is NaN has a zero output and lse = -inf; the other heads are not touched."""
+    q, K = _inputs(heads, 2, 3 + k_t, False)
+    ids = torch.arange(k_t).reshape(1, 1, -1).repeat(2, 1, 1).int()
+    out, lse = _decode(q, K, ids, splits)
+    bad = q.clone()
+    bad[:, 3, 100] = math.nan
+    o2, l2 = _decode(bad, K, ids, splits)
+    assert bool((o2[:, 3] == 0).all()) and bool((l2[:, 3] == -math.inf).all())
+    rest = [h for h in range(heads) if h != 3]
+    assert torch.equal(o2[:, rest], out[:, rest]) and torch.equal(l2[:, rest], lse[:, rest])
+
+
+@pytest.mark.parametrize("k_t,splits", [(40, 1), (500, 0), (1024, 2)])
+def test_nan_row_leaves_its_split_out_with_sixteen_heads(k_t, splits):
+    q, K = _inputs(16, 2, 5 + k_t, False)
+    ids = torch.arange(k_t).reshape(1, 1, -1).repeat(2, 1, 1).int()
+    K[0, 0, 7, 11] = math.nan
+    out, lse = _decode(q, K, ids, splits)
+    assert bool(torch.isfinite(out).all()) and not bool(torch.isnan(lse).any())
