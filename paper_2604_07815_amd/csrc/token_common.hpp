@@ -21,23 +21,19 @@ __device__ inline void unpack_nibbles8(uint32_t w, float* f) {
 __device__ inline uint32_t alpha_key(float a) { return __float_as_uint(fmaxf(a, 0.f)) | 0x80000000u; }
 
 // A packed dword of codes (channel 2i in the low nibble of byte i) as bf16
-// numbers 16 + c (bits 0x4180 | c << 3, exact), in the channel order 0, 2, 1,
-// 3, 4, 6, 5, 7 of a matrix operand.  Eight instructions; 16 is the smallest
-// offset for which one byte permute makes two codes, and 16 sum q~ comes off
-// the dot in fp32 before the row's scale multiplies it (dot16).
+// numbers, in the channel order 0, 2, 4, 6, 1, 3, 5, 7 of a matrix operand.  As
+// an fp8 number (e4m3) a byte c < 16 is c 2^-9, subnormal up to 7 and normal
+// above, so the conversion with a scale of 2^9 gives c itself: seven
+// instructions, and nothing has to come off the dot afterwards.
 __device__ inline uint4 codes_bf16(uint32_t w) {
-  constexpr uint32_t kHi = 0x41414141u;
-  uint32_t lo, hi;
-  asm("v_lshl_or_b32 %0, %1, 3, %2" : "=v"(lo) : "v"(w & 0x0f0f0f0fu), "s"(0x80808080u));
-  asm("v_and_or_b32 %0, %1, %2, %3" : "=v"(hi) : "v"(w >> 1), "v"(0x78787878u), "s"(0x80808080u));
-  return make_uint4(__builtin_amdgcn_perm(kHi, lo, 0x04010400u), __builtin_amdgcn_perm(kHi, hi, 0x04010400u),
-                    __builtin_amdgcn_perm(kHi, lo, 0x04030402u), __builtin_amdgcn_perm(kHi, hi, 0x04030402u));
+  const uint32_t lo = w & 0x0f0f0f0fu, hi = (w >> 4) & 0x0f0f0f0fu;
+  return make_uint4(__builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(lo, 512.0f, false)),
+                    __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(lo, 512.0f, true)),
+                    __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(hi, 512.0f, false)),
+                    __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(hi, 512.0f, true)));
 }
-// sum_c q~_c c_c from the product with 16 + c: the fma rounds once, at the
-// size of the result
-__device__ inline float dot16(float acc, float qsum) { return fmaf(-16.0f, qsum, acc); }
 // channel of position j (< 8) in that order
-__device__ inline int codes_chan(int j) { return (j & 4) | ((j & 1) << 1) | ((j >> 1) & 1); }
+__device__ inline int codes_chan(int j) { return 2 * (j & 3) | (j >> 2); }
 
 // The code contraction of 64 tokens of a wave, one per lane, with up to 4 HS
 // heads on one 32-channel group.  The tokens are four tiles of 16, lane (lg,
@@ -67,7 +63,7 @@ __device__ inline void lane_operands(const uint16_t* s_qt, bf16x8_t (&qa)[HS][4]
   }
 }
 
-// Products of this lane's codes (16 + c each, see dot16) with the heads' q~.
+// Products of this lane's codes with the heads' q~.
 // Every lane of the wave must be active.
 template <int HS>
 __device__ inline void lane_dots(const uint4& c, const bf16x8_t (&qa)[HS][4], f32x4_t (&acc)[HS]) {

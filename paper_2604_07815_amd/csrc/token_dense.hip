@@ -96,13 +96,11 @@ __device__ inline void ds_unit_norm(const float* st, int nc, float (*s_part)[G][
 // ---------------------------------------------------------------------------
 // bf16, G <= 8: a lane owns its tokens, the code contraction runs on the matrix
 // cores (lane_dots).  Bound by HBM (24 bytes per token and pass at d_c = 32) and by
-// vector issue, 93 instructions per 64 tokens: 128 units of 73k tokens, 226
+// vector issue, about 90 instructions per 64 tokens: 128 units of 73k tokens, 226
 // MB, take 45 us (pass 0) and 49 us (pass 1) against 78 us each on the vector
 // units, which spend some 200 instructions on extracting codes and
-// multiply-adds.  Codes entered as plain bf16 integers cost seven more
-// instructions per dword and 8 us per pass for the same error.  A work-group takes kDsSteps steps of
-// four tokens per thread, the next step's rows requested before the last is
-// used.
+// multiply-adds.  A work-group takes kDsSteps steps of four tokens per thread,
+// the next step's rows requested before the last is used.
 // ---------------------------------------------------------------------------
 constexpr int kDsTpt = 4, kDsSteps = 4;
 constexpr int kDsMfmaChunk = kDsThreads * kDsTpt * kDsSteps;
@@ -231,7 +229,7 @@ __global__ __launch_bounds__(kDsThreads, G <= 4 ? 4 : 2) void ds_score_mfma_kern
 #pragma unroll
         for (int h = 0; h < G; ++h) {
           const float qs = qsum[h / 4][h % 4];
-          const float v = sigma2 * fmaf(pr[st & 1][t].x, dot16(acc[h / 4][h % 4], qs), pr[st & 1][t].y * qs);
+          const float v = sigma2 * fmaf(pr[st & 1][t].x, acc[h / 4][h % 4], pr[st & 1][t].y * qs);
           l[t][h] = KEYS ? v - m[h] : v;
         }
       }
@@ -263,7 +261,7 @@ __global__ __launch_bounds__(kDsThreads, G <= 4 ? 4 : 2) void ds_score_mfma_kern
 #pragma unroll
           for (int h = 0; h < G; ++h) {
             const float qs = qsum[h / 4][h % 4];
-            l[t][h] += fmaf(pr[1][t].x, dot16(acc[h / 4][h % 4], qs), pr[1][t].y * qs);
+            l[t][h] += fmaf(pr[1][t].x, acc[h / 4][h % 4], pr[1][t].y * qs);
           }
         }
       }
@@ -414,7 +412,7 @@ __global__ __launch_bounds__(kDsThreads, 2) void ds_score_wide_kernel(
         for (int ht = 0; ht < HT; ++ht) {
           const f32x4_t acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qa[ht][gr], b, f32x4_t{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
 #pragma unroll
-          for (int r = 0; r < 4; ++r) v[ht][r] += fmaf(sc, dot16(acc[r], qs[ht][gr][r]), mn * qs[ht][gr][r]);
+          for (int r = 0; r < 4; ++r) v[ht][r] += fmaf(sc, acc[r], mn * qs[ht][gr][r]);
         }
       }
 #pragma unroll

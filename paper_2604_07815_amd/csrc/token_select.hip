@@ -317,7 +317,7 @@ __global__ __launch_bounds__(256) void token_score_lane_kernel(
 #pragma unroll
     for (int h = 0; h < 4 * HS; ++h) {
       const float qs = qsum[h / 4][h % 4];
-      l[h] += fmaf(pr[gr].x, dot16(acc[h / 4][h % 4], qs), pr[gr].y * qs);
+      l[h] += fmaf(pr[gr].x, acc[h / 4][h % 4], pr[gr].y * qs);
     }
   }
   float* lg = logits + size_t(unit) * G * S + slot;

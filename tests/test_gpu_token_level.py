@@ -170,3 +170,52 @@ def test_tokens_of_given_blocks(G, d, d_c, dtype, k_b, k_t):
             chosen[ids] = True
             assert bool(chosen[alpha > kth * (1 + 1e-5)].all()) and not bool(chosen[alpha < kth * (1 - 1e-5)].any())
             assert torch.allclose(sc[s, u, :kk].double(), alpha[ids], rtol=1e-5, atol=0)
+
+
+@pytest.mark.parametrize("G,d_qk,d_c,mla", [(1, 64, 64, False), (2, 128, 64, False), (4, 128, 64, False), (8, 128, 32, False),
+                                            (8, 128, 128, False), (8, 128, 96, False), (16, 576, 64, True),
+                                            (32, 576, 128, True)])
+def test_codes_enter_the_products_exactly(G, d_qk, d_c, mla):
+    """Channels of code 0 add nothing to a logit, however large the query is there: half of each group has queries of
+    2^16 and codes 0, the rest queries of 1 and all codes, with min = 0 and scale = 1.  Then a logit is off by the
+    additions of its d_c products only, 2^-24 sum |q c| each, and alpha by twice that and the exponentials (2^-20)."""
+    lens = (4096, 700)
+    layout, q, K, V, n, ch, codes, qp = _setup(G, d_qk, d_c, torch.bfloat16, mla, lens, 17 * G + d_c)
+    hkv = K.shape[1]
+    g = torch.Generator(device="cuda").manual_seed(G)
+    c = torch.randint(0, 16, (*codes.shape[:3], d_c), generator=g, device="cuda", dtype=torch.uint8)
+    big = (torch.arange(d_c, device="cuda") // 3) % 2 == 0
+    c[..., big] = 0
+    codes.copy_(c[..., 0::2] | (c[..., 1::2] << 4))
+    qp[..., 0], qp[..., 1] = 1.0, 0.0
+    q = torch.randn(q.shape, generator=g, device="cuda") * 0.2
+    for u in range(hkv):
+        q[:, u * G:(u + 1) * G, ch[u][big].long()] *= 2.0 ** 16
+    q = q.to(torch.bfloat16)
+    k_b = 11 if not mla else 64
+    tids = torch.empty((2, hkv, k_b * 64), dtype=torch.int32, device="cuda")
+    sc = torch.empty((2, hkv, k_b * 64), dtype=torch.float32, device="cuda")
+    if not mla:  # the two-level scores
+        bids = torch.arange(k_b, dtype=torch.int32, device="cuda").reshape(1, 1, -1).repeat(2, hkv, 1)
+        ws = tls.alloc_workspace(layout, k_b, k_b * 64)
+        # (64-token blocks past a length are empty entries)
+        bids[1, :, 11:] = -1
+        tls.tls_select_tokens(layout, q, codes, qp, ch, bids.contiguous(), k_b, n, k_b * 64, tids, sc, ws)
+        assert tls.tls_check_device_error(ws) == 0
+    top = _select(layout, q, K, V, n, ch, codes, qp, 100)  # the token-level operator
+    for s, ln in enumerate(lens):
+        for u in range(hkv):
+            x = c[s, u, :ln].double()
+            qq = q[s, u * G:(u + 1) * G].double()[:, ch[u].long()]
+            tol = 2 * d_c * 2.0 ** -24 * float((qq.abs() @ x.T).max()) / math.sqrt(d_qk) + 2.0 ** -20
+            assert tol < 2e-3
+            if not mla:
+                m = min(ln, k_b * 64)
+                want = torch.softmax(qq @ x[:m].T / math.sqrt(d_qk), -1).mean(0)
+                assert torch.equal(tids[s, u, :m], torch.arange(m, dtype=torch.int32, device="cuda"))
+                assert torch.allclose(sc[s, u, :m].double(), want, rtol=tol, atol=0)
+            want = torch.softmax(qq @ x.T / math.sqrt(d_qk), -1).mean(0)
+            kth = want.sort(descending=True).values[99]
+            chosen = torch.zeros(ln, dtype=torch.bool, device="cuda")
+            chosen[top[s, u].long()] = True
+            assert bool(chosen[want > kth * (1 + 2 * tol)].all()) and not bool(chosen[want < kth * (1 - 2 * tol)].any())
