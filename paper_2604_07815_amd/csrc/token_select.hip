@@ -162,9 +162,12 @@ __device__ inline void write_chunk_stats(const float (*s_red)[NH][2], int G, flo
 // with G = 1, 2, 4 or 8: a latency chain at the sizes it runs at, so the
 // loads leave in two rounds (block-list entry, context length and channel ids;
 // then q~ and the slot's rows) with one barrier, a row is dequantised in
-// registers and meets the heads' q~ of a channel in one LDS read.  The sums of
-// min and scale parts are not kept apart: sum_c q~_c (min + scale code_c) with
-// each term centred rounds less.  2 units of 4 heads, 512 slots: 9.4 -> 4 us.
+// registers and meets the heads' q~ of a channel in one LDS read.  fp32 queries
+// take sum_c q~_c (min + scale code_c) with each term centred, which rounds
+// less than min and scale parts apart (alpha against 64 bits, 4 heads of 128
+// channels: 1.22e-7 rms, 1.89e-7 apart).  2 units of 4 heads, 512 slots: 9.4 ->
+// 4 us; bf16, 256 units of 8 heads, 96 channels, 8192 slots, the whole selection:
+// 202 -> 115.
 template <class E, int G>
 __global__ __launch_bounds__(256) void token_score_row_kernel(
     const typename E::T* __restrict__ q, const uint8_t* __restrict__ codes, const float* __restrict__ qparams,
@@ -172,6 +175,7 @@ __global__ __launch_bounds__(256) void token_score_row_kernel(
     const int32_t* __restrict__ ctx_lens, int H_q, int H_kv, int d, int d_c, int B, int T, float sigma,
     float* __restrict__ logits, float* __restrict__ stats, uint32_t* __restrict__ kinfo, uint32_t* err) {
   __shared__ __attribute__((aligned(16))) float s_q[kMaxGroups * 32 * G];  // [channel][head]
+  __shared__ float s_qs[E::kIsBf16 ? kMaxGroups : 1][G];
   __shared__ float s_red[4][G][2];
   const int unit = blockIdx.y, chunk = blockIdx.x;
   if (chunk == 0 && threadIdx.x == 0) kinfo[2 * size_t(unit)] = 0u;  // arrivals of the alpha stage
@@ -205,7 +209,16 @@ __global__ __launch_bounds__(256) void token_score_row_kernel(
   __builtin_amdgcn_sched_barrier(0);
   if (tid < d_c) {
 #pragma unroll
-    for (int h = 0; h < G; ++h) s_q[tid * G + h] = E::to_f(qv[h]);
+    for (int h = 0; h < G; ++h) {
+      s_q[tid * G + h] = E::to_f(qv[h]);
+      if constexpr (E::kIsBf16) {  // the group's 32 channels are two DPP rows
+        const uint32_t r16 = row16_reduce_bits(__float_as_uint(E::to_f(qv[h])), [](uint32_t u, uint32_t v) {
+          return __float_as_uint(__uint_as_float(u) + __uint_as_float(v));
+        });
+        const auto sw = __builtin_amdgcn_permlane16_swap(r16, r16, false, false);
+        if (tid % 32 == 0) s_qs[tid / 32][h] = __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
+      }
+    }
   }
   lds_barrier();
   float acc[G];
@@ -221,17 +234,25 @@ __global__ __launch_bounds__(256) void token_score_row_kernel(
     }
     const float* qr = s_q + gr * 32 * G;
     const uint32_t wd[4] = {c.x, c.y, c.z, c.w};
+    // the group's sum, rounded at its own size and not at that of all groups;
+    // the products of bf16 queries and codes are exact, so those take the
+    // codes and the sum of q~ apart
+    float part[G];
+#pragma unroll
+    for (int h = 0; h < G; ++h) part[h] = 0.f;
 #pragma unroll
     for (int w = 0; w < 4; ++w) {
       float f[8];
       unpack_nibbles8(wd[w], f);
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
-        const float x = fmaf(p.x, f[e], p.y);
+        const float x = E::kIsBf16 ? f[e] : fmaf(p.x, f[e], p.y);
 #pragma unroll
-        for (int h = 0; h < G; ++h) acc[h] = fmaf(qr[(w * 8 + e) * G + h], x, acc[h]);
+        for (int h = 0; h < G; ++h) part[h] = fmaf(qr[(w * 8 + e) * G + h], x, part[h]);
       }
     }
+#pragma unroll
+    for (int h = 0; h < G; ++h) acc[h] += E::kIsBf16 ? fmaf(p.x, part[h], p.y * s_qs[gr][h]) : part[h];
   }
   float* lg = logits + size_t(unit) * G * S + slot;
 #pragma unroll

@@ -219,3 +219,33 @@ def test_codes_enter_the_products_exactly(G, d_qk, d_c, mla):
             chosen = torch.zeros(ln, dtype=torch.bool, device="cuda")
             chosen[top[s, u].long()] = True
             assert bool(chosen[want > kth * (1 + 2 * tol)].all()) and not bool(chosen[want < kth * (1 - 2 * tol)].any())
+
+
+@pytest.mark.parametrize("G,d_qk,d_c", [(1, 320, 160), (2, 320, 256), (4, 128, 96), (8, 128, 96), (8, 128, 64)])
+def test_a_large_minimum_stays_out_of_the_products(G, d_qk, d_c):
+    """bf16 queries that sum to 0 over each group and rows with minima of 2^13 and scales of 2^-6: the minima cancel
+    exactly where the sum of the queries is formed first, while min + scale * code is rounded at 2^-11.  A logit is then
+    off by a rounding per group, 2^-24 of at most 2^6, and alpha by twice that and the exponentials."""
+    lens = (1300, 700)
+    layout, q, K, V, n, ch, codes, qp = _setup(G, d_qk, d_c, torch.bfloat16, False, lens, 13 * G + d_c)
+    g = torch.Generator(device="cuda").manual_seed(G)
+    codes.copy_(torch.randint(0, 256, codes.shape, generator=g, device="cuda", dtype=torch.uint8))
+    qp[..., 0] = 2.0 ** -6 * (1 + torch.rand(qp.shape[:-1], generator=g, device="cuda"))
+    qp[..., 1] = 2.0 ** 13 * (1 + torch.rand(qp.shape[:-1], generator=g, device="cuda"))
+    half = torch.randint(1, 9, (2, 2 * G, d_c // 2), generator=g, device="cuda") * 0.25  # sums of these are exact
+    pairs = torch.stack([half, -half], -1).reshape(2, 2 * G, d_c)
+    for u in range(2):
+        q[:, u * G:(u + 1) * G, ch[u].long()] = pairs[:, u * G:(u + 1) * G].to(torch.bfloat16)
+    k_b = 21
+    bids = torch.arange(k_b, dtype=torch.int32, device="cuda").reshape(1, 1, -1).repeat(2, 2, 1)
+    bids[1, :, 11:] = -1
+    tids = torch.empty((2, 2, k_b * 64), dtype=torch.int32, device="cuda")
+    sc = torch.empty((2, 2, k_b * 64), dtype=torch.float32, device="cuda")
+    ws = tls.alloc_workspace(layout, k_b, k_b * 64)
+    tls.tls_select_tokens(layout, q, codes, qp, ch, bids.contiguous(), k_b, n, k_b * 64, tids, sc, ws)
+    assert tls.tls_check_device_error(ws) == 0
+    for s, ln in enumerate(lens):
+        for u in range(2):
+            assert torch.equal(tids[s, u, :ln], torch.arange(ln, dtype=torch.int32, device="cuda"))
+            alpha = _alpha(q, codes, qp, ch, ln, s, u, G)
+            assert torch.allclose(sc[s, u, :ln].double(), alpha, rtol=1e-5, atol=0)
