@@ -273,18 +273,25 @@ bool gqa_whole_ok(const Problem& P, int K_t);
 
 int gqa_tokens_per_split(const Problem& P) { return P.dtype == 1 ? kAttnMaxTPWBf16 : kAttnMaxTPW; }
 
+template <class Kernel>
+static int wgs_per_cu(Kernel kern, int threads) {
+  int nb = 0;
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, kern, threads, 0) != hipSuccess || nb < 1) nb = 1;
+  return nb;
+}
+
 // Work-groups of the bf16 kernel resident per compute unit (LDS-bound).
 template <int D, int G>
 static int mfma_wgs_per_cu() {
-  static const int occ = [] {
-    int nb = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
-            &nb, attn_gqa_mfma_kernel<D, G, kAttnNW, kAttnMaxTPWBf16 / kAttnNW, false>, 64 * kAttnNW, 0) !=
-            hipSuccess ||
-        nb < 1)
-      nb = 1;
-    return nb;
-  }();
+  static const int occ =
+      wgs_per_cu(attn_gqa_mfma_kernel<D, G, kAttnNW, kAttnMaxTPWBf16 / kAttnNW, false>, 64 * kAttnNW);
+  return occ;
+}
+
+// The same of the fp32 kernel of one chunk (also LDS-bound: 2 D 256 bytes).
+template <class E, int D, int G>
+static int chunk_wgs_per_cu() {
+  static const int occ = wgs_per_cu(attn_gqa_chunk_kernel<E, D, G>, 256);
   return occ;
 }
 
@@ -308,7 +315,10 @@ static int mfma_wgs_per_cu_g(int G) {
 // 64.6 -> 63.4, 32 of 8192: 39.5 -> 38.4); 160 units of 2048 tokens 0.4 less to
 // 0.4 more, 64 of 8192 0.5 more, 128 of 8192 1.0 more, and in several rounds
 // (256 units of 8192 tokens) 5 to 18 us more.  With 8 heads of 128 between 1.2
-// less and 1.0 more, so those keep the kernel.
+// less and 1.0 more, so those keep the kernel.  fp32 (only the kernel of one
+// chunk merges): 1.0 to 1.4 us less in one round (2 units of 256 tokens 26.4 ->
+// 25.2, 64 of 500 32.6 -> 31.5), 0.4 to 12 more in several (64 units of 1000
+// tokens 43.0 -> 45.0, 128 in 16 splits 63.3 -> 68.8, 256 in 16 102 -> 114).
 constexpr int kFoldColumns = 512;
 constexpr long kFoldFloats = 32768;
 constexpr long kFoldTokens = 1 << 18;
@@ -393,6 +403,7 @@ static bool launch_t(const Problem& P, const void* q, const KvView& kv, const To
   } else {
     tpw = (tpw + kAttnCT - 1) / kAttnCT * kAttnCT;
     if (tpw == kAttnCT) {
+      if (long(P.units) * nsplit > long(device_cus()) * chunk_wgs_per_cu<E, D, G>()) so.arrive = nullptr;
       attn_gqa_chunk_kernel<E, D, G><<<grid, 256, 0, st>>>((const S*)q, (const S*)kv.k, (const S*)kv.v, kv.slot_map,
                                                            kv.n_slots, tl, ctx_lens, P.H_q, P.H_kv, P.T, P.B, P.m_max,
                                                            K_t, tpw, P.sigma, so, err);
