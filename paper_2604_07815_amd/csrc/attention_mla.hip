@@ -96,13 +96,6 @@ __global__ __launch_bounds__(64 * HT * TT, 2) void attn_mla_mfma_kernel(
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int t16 = lane & 15, lg = lane >> 4;
   const int tt = w / HT, ht = w % HT;  // score tile of this wave
-  // this wave's queries: head ht*16 + t16, channels kk*32 + lg*8 .. +8
-  bf16x8_t qb[kMlaPieces / 4];
-  {
-    const uint16_t* qh = q + (size_t(s) * H_q + size_t(g) * G + ht * 16 + t16) * kMlaDqk + lg * 8;
-#pragma unroll
-    for (int kk = 0; kk < kMlaPieces / 4; ++kk) qb[kk] = *reinterpret_cast<const bf16x8_t*>(qh + kk * 32);
-  }
   int n = ctx_lens[s];
   n = n < 0 ? 0 : (n > T ? T : n);
   const int p0 = split * tpw;
@@ -144,6 +137,15 @@ __global__ __launch_bounds__(64 * HT * TT, 2) void attn_mla_mfma_kernel(
       if (lane == 32 && i0 / CT + 1 < nch) lds.valid[i0 / CT + 1] = v1;
     }
     if (i < nch * CT) lds.src[i] = src;
+  }
+  // this wave's queries: head ht*16 + t16, channels kk*32 + lg*8 .. +8, requested
+  // behind the list entries (whose wait would cover them) and in flight with the
+  // first rows
+  bf16x8_t qb[kMlaPieces / 4];
+  {
+    const uint16_t* qh = q + (size_t(s) * H_q + size_t(g) * G + ht * 16 + t16) * kMlaDqk + lg * 8;
+#pragma unroll
+    for (int kk = 0; kk < kMlaPieces / 4; ++kk) qb[kk] = *reinterpret_cast<const bf16x8_t*>(qh + kk * 32);
   }
   if (tid < 2) lds.raise[tid] = 0;
   const size_t ubase = slot_map ? size_t(unit) * size_t(n_slots) * B : size_t(unit) * T;
@@ -333,15 +335,18 @@ int mla_mfma_tokens_per_split() { return kMlaMaxTPW; }
 
 // Split count.  More splits shorten a work-group's chain of 64-token chunks
 // (about 1.9 us each) but each adds a partial of G x 512 floats per unit,
-// written and read back (128 KB of traffic for 32 heads: 0.026 us), so the
-// two are weighed, with at most one work-group per compute unit.  Attention
-// and merge, 32 heads, against the former one work-group per compute unit
-// (b units of K tokens, us): 8 x 2048: 16 splits 18.7, 32 splits 22.3; 16 x
-// 2048: 8 splits 23.4, 16 splits 23.9; 8 x 8192: 32 splits 30.3, 16 splits
-// 31.5, 64 splits 33.8.  With 32 heads a split may be as short as 32 tokens,
-// whose rows take five eighths of a chunk's time to arrive: few units with few
-// tokens (whole two-level step, 64-token splits against these): 1 x 500 39.9 ->
-// 38.5, 2 x 500 40.9 -> 39.4, 3 x 300 39.7 -> 38.8 us.
+// written and read back (128 KB of traffic for 32 heads: 0.026 us, the unit of
+// the costs below), so the two are weighed, with at most one work-group per
+// compute unit.  The merge reads four partials at a time below eight splits and
+// the rest one after another (0.3 us each), and from eight on in two columns of
+// loads.  Attention and merge, 32 heads, against the former one work-group per
+// compute unit (b units of K tokens, us): 8 x 2048: 16 splits 18.7, 32 splits
+// 22.3; 16 x 2048: 8 splits 23.4, 16 splits 23.9; 8 x 8192: 32 splits 30.3, 16
+// splits 31.5, 64 splits 33.8.  With 32 heads a split may be as short as 32
+// tokens, which take half of a chunk's time: few units with few tokens (32-token
+// splits against 64-token ones): 1 x 300 11.6, 13.2; 8 x 300 14.2, 14.9; 4 x 500
+// 13.4, 14.0; but 8 x 500 15.6, 15.0; 1 x 2048 14.9, 14.8; and where the longer
+// splits are four (200 tokens) 13.7, 13.3 with 2 units.
 int mla_mfma_splits(const Problem& P, int K_t) {
   constexpr int kChunk = 64;
   const long chunk_cost = 73 * 32 / P.G;  // in partials of one split and unit
@@ -354,8 +359,8 @@ int mla_mfma_splits(const Problem& P, int K_t) {
   long best_cost = -1;
   for (int ns = need; ns <= max_ns; ++ns) {
     const int tokens = (K_t + ns - 1) / ns;
-    const long chain = tokens <= kChunk / 2 ? chunk_cost * 5 / 8 : (tokens + kChunk - 1) / kChunk * chunk_cost;
-    const long cost = chain + long(ns) * P.units;
+    const long chain = tokens <= kChunk / 2 ? chunk_cost / 2 : (tokens + kChunk - 1) / kChunk * chunk_cost;
+    const long cost = chain + long(ns) * P.units + (ns >= 8 ? ns / 4 : (ns > 4 ? (ns - 4) * 12 : 0));
     if (best_cost < 0 || cost < best_cost) {
       best_cost = cost;
       best = ns;
