@@ -89,9 +89,11 @@ enum {
 /* Number of events tls_decode_opts.stage_events must hold: one before each
  * of the seven stages (block score, block top-k, token score, token
  * normalisation, token top-k, attention, split merge) and one after the
- * last.  A stage that is part of the next one's launch (the normalisation
- * in the token top-k) or of the one before (the merge in the attention)
- * shows as an empty interval. */
+ * last.  A stage that is part of the next one's launch (the normalisation in
+ * the token top-k: 4 and 8 query heads per KV head, 16 and 32 with up to 1024
+ * candidates) or of the one before (the merge in the attention; where one
+ * launch makes the whole token selection, its normalisation and top-k) shows
+ * as an empty interval. */
 #define TLS_NUM_STAGE_EVENTS 8
 
 typedef struct tls_layout {

@@ -76,11 +76,12 @@ hipError_t launch_token_score(const Problem& P, const void* q, const uint8_t* co
                               const int32_t* ctx_lens, float* logits, float* stats, int n_tchunks,
                               uint32_t* kinfo, uint32_t* err, hipStream_t st);
 // alpha keys and the top-K_t.  kinfo: two words per unit, the first cleared by
-// launch_token_score.
+// launch_token_score.  topk_begin (nullable) is recorded before the launch that
+// selects: between the two where the head count takes two, else before the one.
 hipError_t launch_token_alpha_topk(const Problem& P, const float* logits, const float* stats, int n_tchunks,
                                    const int32_t* block_ids, int K_b, const int32_t* ctx_lens, int K_t, uint32_t* keys,
                                    uint32_t* kinfo, int32_t* token_ids, float* token_scores, uint32_t* arrive,
-                                   hipStream_t st);
+                                   hipEvent_t topk_begin, hipStream_t st);
 
 // One work-group per unit: (optional) block top-k from block_scores, then the
 // whole token selection on chip, over the selected blocks or, when

@@ -122,11 +122,9 @@ hipError_t run_token_select(const Problem& P, const tls::Workspace& W, const voi
                                          at<uint32_t>(ws, W.kinfo), err, stream);
   if (e != hipSuccess) return e;
   if (ev) (void)hipEventRecord(ev[0], stream);
-  // the normalisation and the top-k are one launch for most head counts
-  if (ev) (void)hipEventRecord(ev[1], stream);
   return tls::launch_token_alpha_topk(P, at<float>(ws, W.logits), at<float>(ws, W.stats), W.n_tchunks, block_ids, K_b,
                                       ctx_lens, K_t, at<uint32_t>(ws, W.keys), at<uint32_t>(ws, W.kinfo), token_ids,
-                                      token_scores, arrive, stream);
+                                      token_scores, arrive, ev ? ev[1] : nullptr, stream);
 }
 
 }  // namespace

@@ -945,13 +945,14 @@ hipError_t launch_token_score(const Problem& P, const void* q, const uint8_t* co
 hipError_t launch_token_alpha_topk(const Problem& P, const float* logits, const float* stats, int n_tchunks,
                                    const int32_t* block_ids, int K_b, const int32_t* ctx_lens, int K_t, uint32_t* keys,
                                    uint32_t* kinfo, int32_t* token_ids, float* token_scores, uint32_t* arrive,
-                                   hipStream_t st) {
+                                   hipEvent_t topk_begin, hipStream_t st) {
   const int S = K_b * P.B;
   const size_t lds = (topk_scratch_words(1024) + size_t(align4w(K_b))) * sizeof(uint32_t);
   const int ept = (S + 1023) / 1024;
   auto one = [&](auto kern) {
     const hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(kern), lds);
     if (e != hipSuccess) return e;
+    if (topk_begin) (void)hipEventRecord(topk_begin, st);
     kern<<<dim3(ept, P.units), 1024, lds, st>>>(logits, stats, n_tchunks, block_ids, K_b, ctx_lens, P.H_kv, P.B, P.T,
                                                 K_t, keys, kinfo, token_ids, token_scores, arrive);
     return hipGetLastError();
@@ -980,6 +981,7 @@ hipError_t launch_token_alpha_topk(const Problem& P, const float* logits, const 
                                              keys, kinfo);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
+  if (topk_begin) (void)hipEventRecord(topk_begin, st);
   auto go = [&](auto kern) {
     const hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(kern), lds);
     if (e != hipSuccess) return e;

@@ -249,3 +249,46 @@ def test_a_large_minimum_stays_out_of_the_products(G, d_qk, d_c):
             assert torch.equal(tids[s, u, :ln], torch.arange(ln, dtype=torch.int32, device="cuda"))
             alpha = _alpha(q, codes, qp, ch, ln, s, u, G)
             assert torch.allclose(sc[s, u, :ln].double(), alpha, rtol=1e-5, atol=0)
+
+
+@pytest.mark.parametrize("heads,h_kv,k_b,two", [(32, 1, 128, True), (32, 1, 16, False), (64, 8, 128, False)])
+def test_stage_events_around_the_normalisation(heads, h_kv, k_b, two):
+    """The normalisation has an interval of its own where it is a launch of its own (32 heads with more than 1024
+    candidates: 50 MB of logits, at least 6 us at 8 TB/s, beside the few us between two events), else an empty one, as
+    the ones before a given token list."""
+    mla = h_kv == 1
+    b, T, k_t = (48, 8192, 500) if mla else (2, 8192, 500)
+    d, dv = (576, 512) if mla else (128, 128)
+    g = torch.Generator(device="cuda").manual_seed(3)
+    q = torch.randn((b, heads, d), generator=g, device="cuda").to(torch.bfloat16)
+    K = torch.randn((b, h_kv, T, d), generator=g, device="cuda", dtype=torch.bfloat16)
+    V = None if mla else torch.randn((b, h_kv, T, dv), generator=g, device="cuda", dtype=torch.bfloat16)
+    n = torch.full((b,), T, dtype=torch.int32, device="cuda")
+    ch = torch.arange(64, dtype=torch.int32, device="cuda").repeat(h_kv, 1).contiguous()
+    layout = tls.make_layout(b, heads, h_kv, d, dv, T, index_channels=64, dtype=torch.bfloat16, mla_shared_kv=mla)
+    kmax, kmin = (torch.empty((b, h_kv, T // 64, d), dtype=torch.bfloat16, device="cuda") for _ in range(2))
+    codes = torch.empty((b, h_kv, T, 32), dtype=torch.uint8, device="cuda")
+    qp = torch.empty((b, h_kv, T, 2, 2), dtype=torch.float32, device="cuda")
+    tls.tls_build_block_index(layout, K, n, 0, T, kmax, kmin)
+    tls.tls_build_token_index(layout, K, n, ch, 0, T, codes, qp)
+    out = torch.empty((b, heads, dv), dtype=torch.bfloat16, device="cuda")
+    tids = torch.empty((b, h_kv, k_t), dtype=torch.int32, device="cuda")
+    ws = tls.alloc_workspace(layout, k_b, k_t)
+    events = [torch.cuda.Event(enable_timing=True) for _ in range(tls.NUM_STAGE_EVENTS)]
+    for e in events:
+        e.record()
+    handles = [e.cuda_event for e in events]
+
+    def interval(first, given):
+        got = []
+        for _ in range(15):
+            idx = (None,) * 5 if given else (kmax, kmin, codes, qp, ch)
+            tls.tls_sparse_decode(layout, q, tls.KV(K, V), n, *idx, k_b, k_t, None, tids if given else None, out, None,
+                                  None, None if given else tids, ws, stage_events=handles)
+            torch.cuda.synchronize()
+            got.append(events[first].elapsed_time(events[first + 1]) * 1e3)
+        return sorted(got)[7]
+
+    normalisation = interval(3, False)
+    empty = interval(3, True)
+    assert (normalisation > empty + 5) is two, (normalisation, empty)
