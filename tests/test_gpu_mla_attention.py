@@ -129,3 +129,51 @@ def test_nan_row_leaves_its_split_out_with_sixteen_heads(k_t, splits):
     K[0, 0, 7, 11] = math.nan
     out, lse = _decode(q, K, ids, splits)
     assert bool(torch.isfinite(out).all()) and not bool(torch.isnan(lse).any())
+
+
+@pytest.mark.parametrize("heads", [16, 32])
+@pytest.mark.parametrize("splits", [0, 3, 40])
+def test_block_lists_and_the_block_pool(heads, splits):
+    """The same tokens as a list of blocks and as ids over a pool of resident blocks: the bits of the ids on the direct
+    layout.  Empty list entries, a ragged last block, blocks in any pool order."""
+    q, K = _inputs(heads, 2, 60 + splits, False)
+    k_b, m, n_slots = 9, T // 64, 30
+    lens = torch.tensor([T - 21, T - 64], dtype=torch.int32)
+    g = torch.Generator().manual_seed(4)
+    bids = torch.full((2, 1, k_b), -1, dtype=torch.int32)
+    ids = torch.full((2, 1, k_b * 64), -1, dtype=torch.int32)
+    for s in range(2):
+        last = (int(lens[s]) - 1) // 64
+        pick = torch.cat([torch.randperm(last, generator=g)[:k_b - 2 - s], torch.tensor([last])]).sort().values
+        bids[s, 0, :len(pick)] = pick.int()
+        tok = (pick[:, None] * 64 + torch.arange(64)).flatten().int()
+        ids[s, 0, :len(tok)] = torch.where(tok < lens[s], tok, torch.tensor(-1, dtype=torch.int32))
+    layout = tls.make_layout(2, heads, 1, 576, 512, T, index_channels=64, dtype=torch.bfloat16, mla_shared_kv=True)
+
+    def run(kv, bids_in, ids_in, k_b, k_t, mode):
+        ws = tls.alloc_workspace(layout, k_b, k_t)
+        out = torch.empty((2, heads, 512), dtype=torch.bfloat16, device="cuda")
+        lse = torch.empty((2, heads), dtype=torch.float32, device="cuda")
+        tls.tls_sparse_decode(layout, q.cuda(), kv, lens.cuda(), None, None, None, None, None, k_b, k_t, bids_in, ids_in,
+                              out, lse, None, None, ws, attn_splits=splits, mode=mode)
+        assert tls.tls_check_device_error(ws) == 0
+        return out.cpu(), lse.cpu()
+
+    dense = tls.KV(K.cuda(), None)
+    ref = run(dense, None, ids.cuda(), 1, k_b * 64, tls.MODE_TWO_LEVEL)
+    _check(q, K, ids, *ref)
+    slot_map = torch.full((2, 1, m), -1, dtype=torch.int32)
+    pool = torch.zeros((2, 1, n_slots, 64, 576), dtype=torch.bfloat16)
+    for s in range(2):
+        where = torch.randperm(n_slots, generator=g)
+        for i, blk in enumerate(bids[s, 0][bids[s, 0] >= 0].tolist()):
+            slot_map[s, 0, blk] = where[i]
+            rows = K[s, 0, blk * 64:(blk + 1) * 64]
+            pool[s, 0, where[i], :len(rows)] = rows
+    for got in (run(dense, bids.cuda(), None, k_b, 1, tls.MODE_BLOCK_SPARSE),
+                run(tls.KV(pool.cuda(), None, slot_map.cuda(), n_slots), None, ids.cuda(), 1, k_b * 64,
+                    tls.MODE_TWO_LEVEL),
+                run(tls.KV(pool.cuda(), None, slot_map.cuda(), n_slots), bids.cuda(), None, k_b, 1,
+                    tls.MODE_BLOCK_SPARSE)):
+        assert torch.equal(got[0].view(torch.int16), ref[0].view(torch.int16))
+        assert torch.equal(got[1].view(torch.int32), ref[1].view(torch.int32))

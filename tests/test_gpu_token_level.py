@@ -135,9 +135,28 @@ SELECT = [
 @pytest.mark.parametrize("G,d,d_c,dtype", SELECT)
 def test_tokens_of_given_blocks(G, d, d_c, dtype, k_b, k_t):
     """Ragged last blocks, empty list entries, candidate counts that do not fill a work-group."""
-    lens = (700, 1337, 64)
-    layout, q, K, V, n, ch, codes, qp = _setup(G, d, d_c, dtype, False, lens, 3 * G + d_c)
-    b, hkv = K.shape[:2]
+    a = _setup(G, d, d_c, dtype, False, (700, 1337, 64), 3 * G + d_c)
+    check_tokens_of_given_blocks(a, (700, 1337, 64), G, k_b, k_t, tls.alloc_workspace(a[0], k_b, k_t))
+
+
+# more than 1024 candidates: several work-groups hand their keys to the last one (4 and 8 heads), or two launches; and
+# one work-group of 1024 for 16 and 32 heads.  Calls of all sizes on one workspace, whose arrival counts are what the
+# call before left; the last work-group is not full for 17 (1088 slots), 33 and 100.
+@pytest.mark.parametrize("G,d,d_c,dtype,mla", [(4, 128, 64, torch.bfloat16, False), (4, 128, 32, torch.float32, False),
+                                               (8, 128, 64, torch.bfloat16, False), (8, 64, 32, torch.bfloat16, False),
+                                               (8, 128, 96, torch.float32, False), (3, 128, 64, torch.bfloat16, False),
+                                               (16, 576, 64, torch.bfloat16, True), (32, 576, 128, torch.bfloat16, True)])
+def test_many_candidates_on_one_workspace(G, d, d_c, dtype, mla):
+    lens = (7000, 1337, 12345)
+    a = _setup(G, d, d_c, dtype, mla, lens, 5 * G + d_c)
+    ws = tls.alloc_workspace(a[0], 190, 2048)
+    for k_b, k_t in ((100, 2048), (17, 1000), (33, 500), (16, 700), (190, 1500), (17, 1), (100, 64)):
+        check_tokens_of_given_blocks(a, lens, G, k_b, k_t, ws)
+
+
+def check_tokens_of_given_blocks(a, lens, G, k_b, k_t, ws):
+    layout, q, K, V, n, ch, codes, qp = a
+    b, hkv, _, d = K.shape
     g = torch.Generator().manual_seed(k_b)
     bids = torch.full((b, hkv, k_b), -1, dtype=torch.int32)
     for s, ln in enumerate(lens):
@@ -148,7 +167,6 @@ def test_tokens_of_given_blocks(G, d, d_c, dtype, k_b, k_t):
             bids[s, u, :len(pick)] = pick
     tids = torch.full((b, hkv, k_t), -7, dtype=torch.int32, device="cuda")
     sc = torch.empty((b, hkv, k_t), dtype=torch.float32, device="cuda")
-    ws = tls.alloc_workspace(layout, k_b, k_t)
     tls.tls_select_tokens(layout, q, codes, qp, ch, bids.cuda(), k_b, n, k_t, tids, sc, ws)
     assert tls.tls_check_device_error(ws) == 0
     tids, sc = tids.cpu(), sc.cpu()
