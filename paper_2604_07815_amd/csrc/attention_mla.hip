@@ -102,6 +102,18 @@ __global__ __launch_bounds__(64 * HT * TT, 2) void attn_mla_mfma_kernel(
   const int cnt = max(0, min(tpw, K_t - p0));
   const int nch = (cnt + CT - 1) / CT;
 
+  // this wave's queries: head ht*16 + t16, channels kk*32 + lg*8 .. +8, requested
+  // behind the list entries (whose wait would cover them) and in flight with the
+  // first rows; ahead of them where no entry is loaded
+  bf16x8_t qb[kMlaPieces / 4];
+  auto load_q = [&] {
+    const uint16_t* qh = q + (size_t(s) * H_q + size_t(g) * G + ht * 16 + t16) * kMlaDqk + lg * 8;
+#pragma unroll
+    for (int kk = 0; kk < kMlaPieces / 4; ++kk) qb[kk] = *reinterpret_cast<const bf16x8_t*>(qh + kk * 32);
+  };
+  const bool direct = tl.kind == kListAll && !slot_map;  // uniform
+  if (direct) load_q();
+
   // resolve entries to rows of the unit's K base; a skipped entry gathers a
   // valid row of the same chunk (its probability is zero and its values are
   // finite), or row 0 when the chunk has none (the chunk is then not consumed)
@@ -138,15 +150,7 @@ __global__ __launch_bounds__(64 * HT * TT, 2) void attn_mla_mfma_kernel(
     }
     if (i < nch * CT) lds.src[i] = src;
   }
-  // this wave's queries: head ht*16 + t16, channels kk*32 + lg*8 .. +8, requested
-  // behind the list entries (whose wait would cover them) and in flight with the
-  // first rows
-  bf16x8_t qb[kMlaPieces / 4];
-  {
-    const uint16_t* qh = q + (size_t(s) * H_q + size_t(g) * G + ht * 16 + t16) * kMlaDqk + lg * 8;
-#pragma unroll
-    for (int kk = 0; kk < kMlaPieces / 4; ++kk) qb[kk] = *reinterpret_cast<const bf16x8_t*>(qh + kk * 32);
-  }
+  if (!direct) load_q();
   if (tid < 2) lds.raise[tid] = 0;
   const size_t ubase = slot_map ? size_t(unit) * size_t(n_slots) * B : size_t(unit) * T;
   const uint8_t* Kb = reinterpret_cast<const uint8_t*>(Kp + ubase * kMlaDqk);
