@@ -421,12 +421,9 @@ __device__ inline float quad_max(float v) {
 
 constexpr int kIdxBlockRows = 64;  // B of the fast kernel
 
-// Order of the work-groups: heads fastest, as the heads' rows of one token are
-// adjacent in the prefill output; blocks fastest in the form for many blocks of
-// 128-byte rows (launch_index_block_for).
-__host__ __device__ constexpr bool idx_blocks_fastest(int nt) { return nt == 128; }
-
-template <class E, int CPR, int NT, bool VROWS>
+// BF: the work-groups walk a head's blocks first; else the heads of a block, whose
+// rows of one token are adjacent in the prefill output.
+template <class E, int CPR, int NT, bool BF, bool VROWS>
 __global__ __launch_bounds__(NT) void index_block_kernel(const IndexArgs a) {
 #pragma clang fp contract(off)
   using S = typename E::T;
@@ -438,7 +435,6 @@ __global__ __launch_bounds__(NT) void index_block_kernel(const IndexArgs a) {
   extern __shared__ uint4 smem4[];
   uint32_t* t32 = reinterpret_cast<uint32_t*>(smem4);
   int* s_ch = reinterpret_cast<int*>(t32 + kIdxBlockRows * TSW);
-  constexpr bool BF = idx_blocks_fastest(NT);
   const int s = blockIdx.z, g = BF ? blockIdx.y : blockIdx.x, blk = BF ? blockIdx.x : blockIdx.y, tid = threadIdx.x;
   int n = a.ctx_lens[s];
   if (n < 0 || n > a.T) {
@@ -597,37 +593,43 @@ __global__ __launch_bounds__(NT) void index_block_kernel(const IndexArgs a) {
   }
 }
 
-template <class E, int CPR, int NT>
+template <class E, int CPR, int NT, bool BF = false>
 static void launch_index_block(const IndexArgs& a, int nblk, int batch, hipStream_t st) {
   const size_t lds = size_t(kIdxBlockRows) * (CPR * 16 + 16) + size_t(a.d_c) * sizeof(int);
   const unsigned H = unsigned(a.H_kv), nb = unsigned(nblk);
-  const dim3 grid(idx_blocks_fastest(NT) ? nb : H, idx_blocks_fastest(NT) ? H : nb, unsigned(batch));
-  if (a.v_src) index_block_kernel<E, CPR, NT, true><<<grid, NT, lds, st>>>(a);
-  else if constexpr (NT != 128) index_block_kernel<E, CPR, NT, false><<<grid, NT, lds, st>>>(a);
+  const dim3 grid(BF ? nb : H, BF ? H : nb, unsigned(batch));
+  if (a.v_src) index_block_kernel<E, CPR, NT, BF, true><<<grid, NT, lds, st>>>(a);
+  else if constexpr (!BF) index_block_kernel<E, CPR, NT, BF, false><<<grid, NT, lds, st>>>(a);
 }
 
 // The fast kernel's shapes: blocks of 64 rows, K rows of 8, 16, 32 or 72
 // 16-byte pieces, and V rows (if written) as wide as the K rows.
 //
-// A prefill of 128-byte rows with more than two blocks per compute unit takes
-// 128 threads per block, four rows of a column each, and walks the blocks of a
-// head (8 KB of consecutive cache each) first.  Two prompts of 5248 tokens, 8
-// heads of 64, d_c = 64 and 32, on buffers that stay in the Infinity Cache and on
-// others: general kernel 16.0 / 19.7 and 14.5 / 18.0 us, 256 threads with heads
-// first 17.9 / 18.7 and 16.1 / 17.0, this form 16.0 / 16.7 and 13.3 / 14.0 (only
-// the threads 16.9 / 18.2 and 14.1 / 15.5, only the order 17.3 / 18.1 and 15.6 /
-// 16.3).  With two blocks per compute unit the quantiser's rounds of the fewer
-// threads are what is left: two prompts of 2048 9.0 / 10.1 us with 256 threads,
-// 9.6 / 10.7 with 128 (d_c = 64), and so without V: the token index alone of 5248
-// tokens 6.9 and 8.6.
+// A prefill of 128-byte rows with more than two blocks per compute unit walks a
+// head's blocks (8 KB of consecutive cache each) first.  Up to eight per compute
+// unit, where all work-groups are resident at once, it takes 128 threads per
+// block, four rows of a column each in place of two; with more, 256, whose
+// quantiser needs half the rounds.  Measured on buffers that stay in the Infinity
+// Cache / on others, us (general kernel; 256 threads with the heads first; the
+// form taken here; the other number of threads): 2 prompts of 5248 tokens, 8
+// heads, d_c = 64 16.1 / 19.7; 18.0 / 18.7; 15.9 / 16.7; 17.3 / 18.0, d_c = 32
+// 14.4 / 17.9; 16.1 / 16.9; 13.4 / 14.0; 15.6 / 16.2; 8 prompts of 2000 to 4000,
+// d_c = 64 29.7 / 39.5; 28.8 / 32.3; 27.8 / 31.6; 31.4 / 34.6; 8 of 8192 77.4 /
+// 78.8; 59.4 / 63.8; 56.0 / 58.7; 57.9 / 59.5.  With two blocks per compute unit
+// 256 threads with the heads first: 2 prompts of 2048 9.0 / 10.1, with 128 and
+// the blocks first 9.6 / 10.7, with 256 9.4 / 10.2 (d_c = 64); so also without V:
+// the token index alone of 5248 tokens 6.9, 8.6 with 128.
 static bool launch_index_block_for(const Problem& P, const IndexArgs& a, int rb, int nblk, hipStream_t st) {
   if (P.B != kIdxBlockRows || (a.v_src && P.d_v != P.d_qk) || nblk > 65535) return false;
   if (P.dtype == 1) {
     switch (rb / 16) {
-      case 8:
-        if (a.v_src && long(nblk) * P.H_kv * P.b > 2L * device_cus()) launch_index_block<BF16, 8, 128>(a, nblk, P.b, st);
-        else launch_index_block<BF16, 8, 256>(a, nblk, P.b, st);
+      case 8: {
+        const long n = long(nblk) * P.H_kv * P.b, cus = device_cus();
+        if (!a.v_src || n <= 2 * cus) launch_index_block<BF16, 8, 256>(a, nblk, P.b, st);
+        else if (n <= 8 * cus) launch_index_block<BF16, 8, 128, true>(a, nblk, P.b, st);
+        else launch_index_block<BF16, 8, 256, true>(a, nblk, P.b, st);
         return true;
+      }
       case 16: launch_index_block<BF16, 16, 256>(a, nblk, P.b, st); return true;
       case 72: launch_index_block<BF16, 72, 576>(a, nblk, P.b, st); return true;
       default: return false;

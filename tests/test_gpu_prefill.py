@@ -31,10 +31,13 @@ CASES = {
     # key rows of 128 and 256 bytes
     "gqa_d64_bf16": synth.config("qwen3_gqa_48k").replace(batch=2, h_q=8, h_kv=2, d_qk=64, d_v=64, ctx_lo=500,
                                                           ctx_hi=1100, clusters=1, k_b=6, k_t=100, seed=146),
-    # more than two blocks per compute unit, also in the last chunk: the form of 128 threads
+    # more than two blocks per compute unit, also in the last chunk: the form of 128 threads; more than eight in the
+    # whole prompt: 256 threads, blocks first
     "gqa_d64_bf16_many": synth.config("qwen3_gqa_48k").replace(batch=4, h_q=8, h_kv=8, d_qk=64, d_v=64, d_c=64,
                                                                ctx_lo=1900, ctx_hi=2300, clusters=1, k_b=6, k_t=100,
                                                                seed=148),
+    "gqa_d64_bf16_most": synth.config("qwen3_gqa_48k").replace(batch=9, h_q=8, h_kv=8, d_qk=64, d_v=64, ctx_lo=1900,
+                                                               ctx_hi=2000, clusters=1, k_b=6, k_t=100, seed=149),
     "gqa_d64_f32": synth.config("qwen3_gqa_48k").replace(dtype="f32", batch=2, h_q=8, h_kv=2, d_qk=64, d_v=64,
                                                          ctx_lo=500, ctx_hi=1100, clusters=1, k_b=6, k_t=100,
                                                          seed=147),
