@@ -10,9 +10,9 @@
 // flight, and only LDS-side waits separate the stages.  Per chunk: scores
 // (row groups of LPR lanes, reduced with a transposing butterfly), an online
 // softmax update per head, then P.V into register accumulators.  The
-// work-group writes its normalised partial output and log-sum-exp; the merge
-// kernel combines the splits.  HBM-bound: (d_qk + d_v) * sizeof(elem) bytes
-// per token.
+// work-group writes its normalised partial output and log-sum-exp; the unit's
+// last work-group or the merge kernel combines the splits (see kFoldColumns).
+// HBM-bound: (d_qk + d_v) * sizeof(elem) bytes per token.
 #include "attn_gqa_mfma.hpp"
 
 namespace tls {
@@ -317,8 +317,10 @@ static int mfma_wgs_per_cu_g(int G) {
 // (256 units of 8192 tokens) 5 to 18 us more.  With 8 heads of 128 between 1.2
 // less and 1.0 more, so those keep the kernel.  fp32 (only the kernel of one
 // chunk merges): 1.0 to 1.4 us less in one round (2 units of 256 tokens 26.4 ->
-// 25.2, 64 of 500 32.6 -> 31.5), 0.4 to 12 more in several (64 units of 1000
-// tokens 43.0 -> 45.0, 128 in 16 splits 63.3 -> 68.8, 256 in 16 102 -> 114).
+// 25.2, 64 of 500 32.6 -> 31.5).  In several rounds 2 to 12 more with four or
+// more splits (64 units of 1000 tokens 43.0 -> 45.0, 128 in 16 splits 63.3 ->
+// 68.8, 256 in 16 102 -> 114); with two or three, which need 512 units and up to
+// 192 tokens, 1.8 less (4 heads of 64) to 7 more (1 head of 128).
 constexpr int kFoldColumns = 512;
 constexpr long kFoldFloats = 32768;
 constexpr long kFoldTokens = 1 << 18;
